@@ -91,6 +91,7 @@ struct Engine {
     double* d_partial = nullptr;
     double* d_h3 = nullptr;
     double* d_mass = nullptr;
+    double* h_mass = nullptr;   // pinned (nbox): the masses come back in one copy
     int* d_flags = nullptr;
     hipStream_t stream = nullptr;
     int device = 0;
@@ -109,12 +110,14 @@ struct Engine {
     void* fv = nullptr;
     void* fw = nullptr;
     // drop labelling: labels and counts (one int per cell of the largest box
-    // labelled so far), the root list (cap entries each) and its length
+    // labelled so far); counters, drops (pairs) and tile roots in one array
+    // (DROPS_HEAD + 3 list_cap ints); the host side of its head, pinned
     int* d_lab = nullptr;
     int* d_cnt = nullptr;
     int64_t lab_n = 0;
     int* d_list = nullptr;
     int64_t list_cap = 0;
+    int* h_list = nullptr;
 };
 
 void free_engine(Engine& e)
@@ -131,6 +134,8 @@ void free_engine(Engine& e)
                     e.d_list};
     for (void* p : bufs)
         if (p) (void)hipFree(p);
+    if (e.h_list) (void)hipHostFree(e.h_list);
+    if (e.h_mass) (void)hipHostFree(e.h_mass);
 }
 
 ch_status init_engine(Engine& e, int nbox, const ch_grid* g, const double* Cn, const double* Pe,
@@ -632,6 +637,10 @@ ch_status run_steps(Engine& e, const void* u, const void* v, const void* w, doub
     return CH_OK;
 }
 
+// Drop lists: ints before the drops (two counters), and the drops that come
+// back with the counters in one copy.
+constexpr int DROPS_HEAD = 2, DROPS_SOON = 1024;
+
 // Drops of box `box`: labels, counts and the sorted (root, cells) list.
 ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, int64_t* root,
                 int64_t* cells)
@@ -656,55 +665,62 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
         }
         e.lab_n = n;
     }
+    if (!e.h_list && hipHostMalloc((void**)&e.h_list, sizeof(int) * (DROPS_HEAD + 2 * DROPS_SOON),
+                                   hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        e.h_list = nullptr;
+        return fail(CH_ENOMEM, "cannot allocate the drop list");
+    }
     const size_t es = chp::esize(e.P.prec);
     const void* C = (const char*)e.C + d.c_off * es;
     const int bc[3] = {d.bc[0], d.bc[1], d.bc[2]};
-    hipError_t err = e.P.prec == CH_FP64
-        ? chk::launch_drops_label<double>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab)
-        : chk::launch_drops_label<float>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab);
-    if (err != hipSuccess) return fail(CH_EHIP, "drop labelling failed: %s", hipGetErrorString(err));
-    HIP_TRY(hipMemsetAsync(e.d_cnt, 0, sizeof(int) * n, e.stream));
-    // the root list: sized from a first pass if the cached one is too short
-    int64_t want = std::max<int64_t>(e.list_cap, 1024);
+    // the list of tile roots: sized from a first pass if the cached one is too short
+    int64_t want = std::max<int64_t>(std::max<int64_t>(e.list_cap, DROPS_SOON), n / 256);
     for (int pass = 0; pass < 2; ++pass) {
         if (want > e.list_cap) {
             if (e.d_list) (void)hipFree(e.d_list);
             e.d_list = nullptr;
             e.list_cap = 0;
-            if (hipMalloc(&e.d_list, sizeof(int) * (2 * want + 1)) != hipSuccess) {
+            if (hipMalloc(&e.d_list, sizeof(int) * (DROPS_HEAD + 3 * want)) != hipSuccess) {
                 (void)hipGetLastError();
                 return fail(CH_ENOMEM, "cannot allocate the drop list");
             }
             e.list_cap = want;
         }
-        int* count = e.d_list + 2 * e.list_cap;
-        HIP_TRY(hipMemsetAsync(count, 0, sizeof(int), e.stream));
-        if (pass == 1) HIP_TRY(hipMemsetAsync(e.d_cnt, 0, sizeof(int) * n, e.stream));
-        err = chk::launch_drops_count(e.stream, e.d_lab, n, e.d_cnt, (int)e.list_cap, e.d_list,
-                                      e.d_list + e.list_cap, count);
+        int* meta = e.d_list;
+        int* out = e.d_list + DROPS_HEAD;
+        int* list = out + 2 * e.list_cap;
+        HIP_TRY(hipMemsetAsync(meta, 0, sizeof(int) * DROPS_HEAD, e.stream));
+        const hipError_t err = e.P.prec == CH_FP64
+            ? chk::launch_drops<double>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab,
+                                        e.d_cnt, meta, list, (int)e.list_cap, out)
+            : chk::launch_drops<float>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab,
+                                       e.d_cnt, meta, list, (int)e.list_cap, out);
         if (err != hipSuccess)
-            return fail(CH_EHIP, "drop counting failed: %s", hipGetErrorString(err));
-        int found = 0;
-        HIP_TRY(hipMemcpyAsync(&found, count, sizeof(int), hipMemcpyDeviceToHost, e.stream));
+            return fail(CH_EHIP, "drop labelling failed: %s", hipGetErrorString(err));
+        // the counters and the first drops in one copy
+        HIP_TRY(hipMemcpyAsync(e.h_list, e.d_list, sizeof(int) * (DROPS_HEAD + 2 * DROPS_SOON),
+                               hipMemcpyDeviceToHost, e.stream));
         HIP_TRY(hipStreamSynchronize(e.stream));
-        if (found <= e.list_cap) {
-            std::vector<int> r(found), c(found);
-            if (found > 0) {
-                HIP_TRY(hipMemcpy(r.data(), e.d_list, sizeof(int) * found, hipMemcpyDeviceToHost));
-                HIP_TRY(hipMemcpy(c.data(), e.d_list + e.list_cap, sizeof(int) * found,
+        if (e.h_list[0] <= e.list_cap) {
+            const int found = e.h_list[1];
+            std::vector<std::pair<int, int>> r(found);
+            if (found <= DROPS_SOON) {
+                if (found > 0)
+                    memcpy((void*)r.data(), e.h_list + DROPS_HEAD, sizeof(int) * 2 * found);
+            } else {
+                HIP_TRY(hipMemcpy((void*)r.data(), out, sizeof(int) * 2 * found,
                                   hipMemcpyDeviceToHost));
             }
-            std::vector<int> order(found);
-            for (int q = 0; q < found; ++q) order[q] = q;
-            std::sort(order.begin(), order.end(), [&](int a, int b) { return r[a] < r[b]; });
+            std::sort(r.begin(), r.end());
             for (int64_t q = 0; q < std::min<int64_t>(cap, found); ++q) {
-                root[q] = r[order[q]];
-                cells[q] = c[order[q]];
+                root[q] = r[q].first;
+                cells[q] = r[q].second;
             }
             *ndrops = found;
             return CH_OK;
         }
-        want = found;
+        want = e.h_list[0];
     }
     return fail(CH_EHIP, "drop list did not settle");
 }
@@ -827,9 +843,16 @@ ch_status mass(Engine& e, double* out)
         : chk::launch_mass<float>(e.P.nmblk, e.P.nbox, e.stream, e.d_boxes, e.C, e.d_partial,
                                   e.d_h3, e.d_mass);
     if (err != hipSuccess) return fail(CH_EHIP, "mass kernel failed: %s", hipGetErrorString(err));
-    HIP_TRY(hipMemcpyAsync(out, e.d_mass, sizeof(double) * e.P.nbox, hipMemcpyDeviceToHost,
+    if (!e.h_mass && hipHostMalloc((void**)&e.h_mass, sizeof(double) * e.P.nbox,
+                                   hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        e.h_mass = nullptr;   // the copy goes straight to the caller's array
+    }
+    double* dst = e.h_mass ? e.h_mass : out;
+    HIP_TRY(hipMemcpyAsync(dst, e.d_mass, sizeof(double) * e.P.nbox, hipMemcpyDeviceToHost,
                            e.stream));
     HIP_TRY(hipStreamSynchronize(e.stream));
+    if (dst != out) memcpy(out, dst, sizeof(double) * e.P.nbox);
     return CH_OK;
 }
 
