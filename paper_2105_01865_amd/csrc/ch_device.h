@@ -1596,6 +1596,303 @@ CH_HD void pass_x_row_program(X& ex, XRowState<T, A>* st, const BoxDesc& bd, con
 }
 
 // ---------------------------------------------------------------------------
+// The explicit 25-point scheme in the manner of pass_x_row_program: one x-line
+// per task, one cell per thread, the y stencil in registers, the next plane's
+// loads into the working registers (the same arithmetic as the explicit mode
+// of pass_x_program, which the plan takes where this one does not apply).
+//
+// There is no solve; C + RHS is written to Q.  The mixed second differences:
+//   xy  the rows y -+ 1 of the plane go through LDS with one halo column a side;
+//   xz  the row at z + 1 is in LDS one plane early (two row buffers that
+//       alternate), its x difference is formed once and carried down: it is
+//       the owned row's at the next plane and the row below's at the one after;
+//   yz  formed one plane behind from the rows y -+ 1 of three planes
+//       (registers).
+//
+// What bounds it: as the row program, vector instruction issue and the latency
+// of its loads (72 VGPRs in single precision, 7 waves per SIMD; 113 in double).
+// The general program put seven rows of C through LDS per plane and kept a
+// second register set for the next plane.  256^3 FP32: 131 against 207 us per
+// launch, the step 0.400 against 0.62 ms (0.65 of a copy's rate for the 19
+// element accesses per point and step, 0.42 before).
+//
+// LDS:
+//   cr: 2 x (nx + 6) T   C of the owned row at two planes, columns -3 .. nx+2
+//   mr, ym, yp, zm: (nx + 2) T   psi'(C) of the owned row, C of the rows y -+ 1
+//                        and (the task's first plane) of the owned row at z - 1,
+//                        columns -1 .. nx
+//   fr: (nx + 1) T       flux through x face f
+// ---------------------------------------------------------------------------
+struct XE25Layout {
+    size_t cr, mr, ym, yp, zm, fr, total;   // byte offsets and total size
+};
+
+CH_HD XE25Layout x_e25_layout(int nx, int sT)
+{
+    XE25Layout L;
+    const size_t narrow = al16((size_t)(nx + 2) * sT);
+    L.cr = 0;
+    L.mr = al16((size_t)2 * (nx + 6) * sT);
+    L.ym = L.mr + narrow;
+    L.yp = L.ym + narrow;
+    L.zm = L.yp + narrow;
+    L.fr = L.zm + narrow;
+    L.total = al16(L.fr + (size_t)(nx + 1) * sT);
+    return L;
+}
+
+template <typename T>
+struct XE25State {
+    T c[7];                   // C at z-3 .. z+3 of the owned cell
+    T mq[3];                  // psi'(C) at z-1, z, z+1
+    T yh[6];                  // C of this plane at rows y-3, y-2, y-1, y+1, y+2, y+3
+    T ul, vl, vh, wl, wh;     // face velocities (as in XRowState)
+    T fzl;                    // flux through the low z face
+    T eold;                   // N of the previous substage at the plane whose RHS is next
+    T py, pz, plap, pb4;      // y and z flux differences, Laplacian of psi', sum of D4
+    T pmix;                   // xy + xz mixed differences of the plane
+    T dxm, dx0;               // second x differences at z-1 and z
+    T hm[2], hp[2];           // C of the rows y-1 and y+1 at the two planes below
+    T nc;                     // C at z+4 of the owned cell
+    int cxp, cxm;             // halo columns fed by the owned column (or the column itself)
+};
+
+template <typename T, class X>
+CH_HD void pass_x_e25_row_program(X& ex, XE25State<T>* st, const BoxDesc& bd, const PassArgs& pa,
+                                  int task, const T* __restrict__ C, const T* __restrict__ U,
+                                  const T* __restrict__ V, const T* __restrict__ W,
+                                  T* __restrict__ E, T* __restrict__ Q, unsigned char* smem)
+{
+    const XZTask t = xz_task(bd, task);
+    const int nx = bd.n[0], ny = bd.n[1], nz = bd.n[2];
+    const int fx = bd.nf[0], fy = bd.nf[1], fz = bd.nf[2];
+    const int bcx = bd.bc[0], k = pa.k;
+    const XE25Layout L = x_e25_layout(nx, (int)sizeof(T));
+    constexpr uint32_t sT = sizeof(T);
+    T* crb = reinterpret_cast<T*>(smem + L.cr) + 3;   // buffer b: crb[b (nx + 6) + x]
+    T* mr = reinterpret_cast<T*>(smem + L.mr) + 1;
+    T* ym = reinterpret_cast<T*>(smem + L.ym) + 1;
+    T* yp = reinterpret_cast<T*>(smem + L.yp) + 1;
+    T* zm = reinterpret_cast<T*>(smem + L.zm) + 1;
+    T* fr = reinterpret_cast<T*>(smem + L.fr);
+    const uint32_t pbytes = (uint32_t)((int64_t)nx * ny * sT);
+    const uint32_t ubytes = (uint32_t)((int64_t)ny * fx * sT);
+    const uint32_t vbytes = (uint32_t)((int64_t)fy * nx * sT);
+    const PlaneRef<T> Cr(C + bd.c_off, (uint32_t)((int64_t)pbytes * nz));
+    const PlaneRef<T> Ur(U + bd.u_off, (uint32_t)((int64_t)ubytes * nz));
+    const PlaneRef<T> Vr(V + bd.v_off, (uint32_t)((int64_t)vbytes * nz));
+    const PlaneRef<T> Wr(W + bd.w_off, (uint32_t)((int64_t)pbytes * fz));
+    const PlaneRef<T> Er(E + bd.c_off, (uint32_t)((int64_t)pbytes * nz));
+    const PlaneRef<T> Qr(Q + bd.c_off, (uint32_t)((int64_t)pbytes * nz));
+    const T epsw = T(bd.eps * (12.0 / 13.0));
+    const T gdt = T(bd.gdt[k]), rdt = T(bd.rdt[k]), bdt = T(bd.bdt[k]);
+    const T inv_h = T(bd.inv_h), lap_s = T(bd.inv_h2 * bd.inv_pe);
+    const Cubic<T> mu = cubic<T>(bd.psi);
+    const int z0 = t.z0, nzc = t.nzc, y = t.y0;
+    // byte offsets within a plane: the row of C (v, w, E), of u, of v's high
+    // face, and the halo rows y-3, y-2, y-1, y+1, y+2, y+3
+    const uint32_t yoff = (uint32_t)(y * nx) * sT, yoffu = (uint32_t)(y * fx) * sT;
+    const uint32_t vtop = (uint32_t)((y + 1 == ny && bd.bc[1] == 0 ? 0 : y + 1) * nx) * sT;
+    uint32_t hoff[6];
+#pragma unroll
+    for (int hr = 0; hr < 6; ++hr)
+        hoff[hr] = (uint32_t)(map_idx(y + (hr < 3 ? hr - 3 : hr - 2), ny, bd.bc[1]) * nx) * sT;
+    auto cplane = [&](int z) { return (uint32_t)map_idx(z, nz, bd.bc[2]) * pbytes; };
+    auto col = [&](int tid) { return tid < nx ? tid : nx - 1; };
+    // the loads of plane z (as in the row program: each group behind the last
+    // use of the previous plane's; u, w and the old N non-temporal)
+    auto load_u = [&](XE25State<T>& s, uint32_t xb, int z) {
+        s.ul = Ur.nt(xb + yoffu, (uint32_t)z * ubytes);
+    };
+    auto load_vy = [&](XE25State<T>& s, uint32_t xb, int z) {
+        const uint32_t zo = (uint32_t)z * pbytes;
+        s.vl = Vr(xb + yoff, (uint32_t)z * vbytes);
+        s.vh = Vr(xb, (uint32_t)z * vbytes + vtop);
+#pragma unroll
+        for (int hr = 0; hr < 6; ++hr) s.yh[hr] = Cr(xb, zo + hoff[hr]);
+    };
+    auto load_wh = [&](XE25State<T>& s, uint32_t xb, int z) {
+        s.wh = Wr.nt(xb + yoff,
+                     (uint32_t)((z + 1 == nz && bd.bc[2] == 0) ? 0 : z + 1) * pbytes);
+    };
+    // the mixed yz difference of a plane: rows y-1 and y+1 at the planes below
+    // (queue), on and above it, and the owned column c0, c1, c2 there
+    auto yz_of = [&](const XE25State<T>& s, T hm2, T hp2, T c0, T c1, T c2) {
+        const T lo = (s.hm[0] - s.hm[1]) + (hm2 - s.hm[1]);
+        const T mid = (c0 - c1) + (c2 - c1);
+        const T hi = (s.hp[0] - s.hp[1]) + (hp2 - s.hp[1]);
+        return (lo + hi) - T(2) * mid;
+    };
+    // C + dt (gamma N + rho N_old) of plane zs, cc the C of the cell there
+    auto rhs_plane = [&](XE25State<T>& s, int x, bool live, int zs, T yz, T cc) {
+        const T fhi = x + 1 < nx ? fr[x + 1] : fr[bcx == 0 ? 0 : nx];
+        const T adv = ((fhi - fr[x]) + s.py) + s.pz;
+        const T e = -adv * inv_h + s.plap * lap_s;
+        const T nk = e - bdt * (s.pb4 + T(2) * (s.pmix + yz));
+        T rhs = gdt * nk;
+        if (pa.e_mode != 0) rhs += rdt * s.eold;
+        if (live) {
+            const uint32_t o = (uint32_t)x * sT + yoff, zo = (uint32_t)(z0 + zs) * pbytes;
+            if (pa.e_mode != 2) Er.store(o, zo, nk);
+            Qr.store(o, zo, cc + rhs);
+        }
+    };
+    auto d2x = [](const T* q) { return (q[-1] - q[0]) + (q[1] - q[0]); };
+
+    ex.phase([&](int tid) {
+        XE25State<T>& s = st[ex.slot(tid)];
+        const int x = col(tid);
+        const uint32_t xb = (uint32_t)x * sT;
+        s.cxp = x;
+        s.cxm = x;
+        for (int q = 0; q < 6; ++q) {
+            const int hc = q < 3 ? q - 3 : nx + q - 3;
+            if (map_idx(hc, nx, bcx) == x) {
+                s.cxp = hc;
+                if (q == 2 || q == 3) s.cxm = hc;
+            }
+        }
+#pragma unroll
+        for (int q = 1; q < 7; ++q) s.c[q] = Cr(xb + yoff, cplane(z0 - 4 + q));
+        s.hm[0] = s.hp[0] = T(0);   // not read before two planes have passed
+        s.hm[1] = Cr(xb, cplane(z0 - 1) + hoff[2]);
+        s.hp[1] = Cr(xb, cplane(z0 - 1) + hoff[3]);
+        s.mq[1] = mu(s.c[3]);
+        s.mq[2] = mu(s.c[4]);
+        wait_loads();
+        s.nc = Cr(xb + yoff, cplane(z0 + 3));
+        load_u(s, xb, z0);
+        load_vy(s, xb, z0);
+        s.wl = Wr(xb + yoff, (uint32_t)z0 * pbytes);
+        load_wh(s, xb, z0);
+    });
+
+    for (int zs = 0; zs < nzc; ++zs) {
+        const int z = z0 + zs;
+        // the owned row at z and at z + 1
+        T* const r0 = crb + (zs & 1) * (nx + 6);
+        T* const r1 = crb + ((zs + 1) & 1) * (nx + 6);
+        // ---- this plane's loads in, the RHS of the plane below, rows into LDS
+        ex.phase([&](int tid) {
+            XE25State<T>& s = st[ex.slot(tid)];
+            const int x = col(tid);
+            const bool live = tid < nx;
+            const uint32_t xb = (uint32_t)x * sT;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) s.c[q] = s.c[q + 1];
+            s.c[6] = s.nc;
+            s.nc = Cr(xb + yoff, cplane(zs + 1 < nzc ? z + 4 : z + 3));
+            if (zs > 0)
+                rhs_plane(s, x, live, zs - 1, yz_of(s, s.yh[2], s.yh[3], s.c[1], s.c[2], s.c[3]),
+                          s.c[2]);
+            s.hm[0] = s.hm[1];
+            s.hm[1] = s.yh[2];
+            s.hp[0] = s.hp[1];
+            s.hp[1] = s.yh[3];
+            sched_fence();
+            if (pa.e_mode != 0) s.eold = Er.nt(xb + yoff, (uint32_t)z * pbytes);
+            s.mq[0] = s.mq[1];
+            s.mq[1] = s.mq[2];
+            s.mq[2] = mu(s.c[4]);
+            if (live) {
+                if (zs == 0) {
+                    r0[x] = s.c[3];
+                    r0[s.cxp] = s.c[3];
+                    zm[x] = s.c[2];
+                    zm[s.cxm] = s.c[2];
+                }
+                r1[x] = s.c[4];
+                r1[s.cxp] = s.c[4];
+                mr[x] = s.mq[1];
+                mr[s.cxm] = s.mq[1];
+                ym[x] = s.yh[2];
+                ym[s.cxm] = s.yh[2];
+                yp[x] = s.yh[3];
+                yp[s.cxm] = s.yh[3];
+            }
+        });
+        // ---- face fluxes, Laplacian of psi'(C), fourth and mixed differences
+        ex.phase([&](int tid) {
+            XE25State<T>& s = st[ex.slot(tid)];
+            const int x = col(tid);
+            const bool live = tid < nx;
+            const T* row = r0 + x;
+            {
+                const T dX[5] = {row[-2] - row[-3], row[-1] - row[-2], row[0] - row[-1],
+                                 row[1] - row[0], row[2] - row[1]};
+                const T f = flux_weno_d<T>(s.ul, dX[0], dX[1], dX[2], dX[3], dX[4], row[-1],
+                                           row[0], epsw);
+                if (live) fr[x] = f;
+                s.pb4 = d4_d<T>(dX[1], dX[2], dX[3], dX[4]);
+                if (zs == 0) {
+                    s.dx0 = d2x(row);
+                    s.dxm = d2x(zm + x);
+                }
+                const T dxp = d2x(r1 + x);
+                const T xy = (d2x(ym + x) + d2x(yp + x)) - T(2) * s.dx0;
+                const T xz = (s.dxm + dxp) - T(2) * s.dx0;
+                s.pmix = xy + xz;
+                s.dxm = s.dx0;
+                s.dx0 = dxp;
+            }
+            pin(s.pmix);
+            const int zn = uniform_i(zs + 1 < nzc ? z + 1 : z);
+            sched_fence();
+            load_u(s, (uint32_t)x * sT, zn);
+            if (bcx != 0 && live && x == nx - 1) {
+                const T uw = Ur((uint32_t)(x + 1) * sT + yoffu, (uint32_t)z * ubytes);
+                fr[nx] = uw * face_weno<T>(uw, row[-2], row[-1], row[0], row[1], row[2], row[3],
+                                           epsw);
+            }
+            {
+                const T yc[7] = {s.yh[0], s.yh[1], s.yh[2], s.c[3], s.yh[3], s.yh[4], s.yh[5]};
+                T dY[6];
+#pragma unroll
+                for (int j = 0; j < 6; ++j) dY[j] = yc[j + 1] - yc[j];
+                const T fyl =
+                    flux_weno_d<T>(s.vl, dY[0], dY[1], dY[2], dY[3], dY[4], yc[2], yc[3], epsw);
+                const T fyh =
+                    flux_weno_d<T>(s.vh, dY[1], dY[2], dY[3], dY[4], dY[5], yc[3], yc[4], epsw);
+                s.py = fyh - fyl;
+                s.pb4 += d4_d<T>(dY[1], dY[2], dY[3], dY[4]);
+            }
+            T myy = mu(s.yh[3]) + mu(s.yh[2]);
+            pin(myy);
+            pin(s.py);
+            sched_fence();
+            load_vy(s, (uint32_t)x * sT, zn);
+            {
+                const T* c = s.c;
+                T dZ[5];
+#pragma unroll
+                for (int j = 0; j < 5; ++j) dZ[j] = c[j + 2] - c[j + 1];
+                if (zs == 0)
+                    s.fzl = flux_weno_d<T>(s.wl, c[1] - c[0], c[2] - c[1], c[3] - c[2],
+                                           c[4] - c[3], c[5] - c[4], c[2], c[3], epsw);
+                const T fzh =
+                    flux_weno_d<T>(s.wh, dZ[0], dZ[1], dZ[2], dZ[3], dZ[4], c[3], c[4], epsw);
+                s.pz = fzh - s.fzl;
+                s.fzl = fzh;
+                s.pb4 += d4_d<T>(dZ[0], dZ[1], dZ[2], dZ[3]);
+            }
+            pin(s.pz);
+            sched_fence();
+            s.wl = s.wh;
+            load_wh(s, (uint32_t)x * sT, zn);
+            s.plap = ((mr[x + 1] + mr[x - 1]) + myy) + (s.mq[2] + s.mq[0]) - T(6) * s.mq[1];
+        });
+    }
+    // ---- RHS of the last plane: rows y -+ 1 at the plane above the chunk
+    ex.phase([&](int tid) {
+        XE25State<T>& s = st[ex.slot(tid)];
+        const int x = col(tid);
+        const uint32_t xb = (uint32_t)x * sT, zo = cplane(z0 + nzc);
+        const T hm2 = Cr(xb, zo + hoff[2]), hp2 = Cr(xb, zo + hoff[3]);
+        rhs_plane(s, x, tid < nx, nzc - 1, yz_of(s, hm2, hp2, s.c[2], s.c[3], s.c[4]), s.c[3]);
+    });
+}
+
+// ---------------------------------------------------------------------------
 // Pass X over one row and one x segment per task, for periodic lines too long
 // for one work-group (the arithmetic of pass_x_row_program, cell by cell).
 //

@@ -25,6 +25,12 @@ hipError_t launch_pass_x_seg(int nwg, int nth, size_t lds, hipStream_t st,
                              const void* C, const void* U, const void* V, const void* W,
                              const void* Ein, void* Eout, void* Q);
 
+// The explicit 25-point scheme's row program (one box; at most 64 KB of LDS).
+template <typename T>
+hipError_t launch_pass_x_e25(int nwg, int nth, size_t lds, hipStream_t st,
+                             const chd::BoxDesc* boxes, const chd::PassArgs& pa, const void* C,
+                             const void* U, const void* V, const void* W, void* E, void* Q);
+
 template <typename T, typename A>
 hipError_t launch_pass_line(int pass, int nwg, int nthreads, size_t lds, hipStream_t st,
                             const chd::BoxDesc* boxes, int nbox, const chd::PassArgs& pa,

@@ -99,6 +99,21 @@ k_pass_x_seg(const chd::BoxDesc* __restrict__ boxes, int nbox, chd::PassArgs pa,
                                                 Eout, Q, smem);
 }
 
+// The explicit 25-point scheme's row program (pass_x_e25_row_program).
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT)
+k_pass_x_e25(const chd::BoxDesc* __restrict__ boxes, chd::PassArgs pa, const T* __restrict__ C,
+             const T* __restrict__ U, const T* __restrict__ V, const T* __restrict__ W,
+             T* __restrict__ E, T* __restrict__ Q)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int task = xcd_task(blockIdx.x, gridDim.x);
+    chd::GpuExec ex{(int)threadIdx.x, (int)blockDim.x};
+    chd::XE25State<T> st;
+    chd::pass_x_e25_row_program<T, chd::GpuExec>(ex, &st, boxes[0], pa, task, C, U, V, W, E, Q,
+                                                 smem);
+}
+
 template <typename T, typename A, int PASS>
 __global__ void __launch_bounds__(512)
 k_pass_line(const chd::BoxDesc* __restrict__ boxes, int nbox, chd::PassArgs pa,
@@ -1383,6 +1398,22 @@ hipError_t launch_pass_x_seg(int nwg, int nth, size_t lds, hipStream_t st,
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_pass_x_e25(int nwg, int nth, size_t lds, hipStream_t st,
+                             const chd::BoxDesc* boxes, const chd::PassArgs& pa, const void* C,
+                             const void* U, const void* V, const void* W, void* E, void* Q)
+{
+    auto go = [&](auto nt) {
+        hipLaunchKernelGGL((k_pass_x_e25<T, decltype(nt)::value>), dim3(nwg), dim3(nth), lds, st,
+                           boxes, pa, (const T*)C, (const T*)U, (const T*)V, (const T*)W, (T*)E,
+                           (T*)Q);
+        return hipGetLastError();
+    };
+    if (nth <= 256) return go(chd::IC<256>{});
+    if (nth <= 512) return go(chd::IC<512>{});
+    return go(chd::IC<1024>{});
+}
+
 template <typename T, typename A>
 hipError_t launch_pass_line(int pass, int nwg, int nthreads, size_t lds, hipStream_t st,
                             const chd::BoxDesc* boxes, int nbox, const chd::PassArgs& pa,
@@ -1604,6 +1635,12 @@ CH_INSTANTIATE(double, double)
 CH_INSTANTIATE(float, float)
 CH_INSTANTIATE(float, double)
 
+template hipError_t launch_pass_x_e25<double>(int, int, size_t, hipStream_t, const chd::BoxDesc*,
+                                              const chd::PassArgs&, const void*, const void*,
+                                              const void*, const void*, void*, void*);
+template hipError_t launch_pass_x_e25<float>(int, int, size_t, hipStream_t, const chd::BoxDesc*,
+                                             const chd::PassArgs&, const void*, const void*,
+                                             const void*, const void*, void*, void*);
 template hipError_t launch_mass<double>(int, int, hipStream_t, const chd::BoxDesc*, const void*,
                                         double*, const double*, double*);
 template hipError_t launch_mass<float>(int, int, hipStream_t, const chd::BoxDesc*, const void*,

@@ -275,9 +275,12 @@ hipError_t enqueue_substage_e25(Engine& e, int k, const void* u, const void* v, 
         if (a) (void)hipEventRecord(a, e.stream);
     }
     const chd::PassArgs pa = chp::pass_args(e.P, k, 0);
-    hipError_t err = chk::launch_pass_x<T, T>(e.P.mi, e.P.ntask[0], e.P.x_threads, e.P.lds[0],
-                                              e.stream, e.d_boxes, e.P.nbox, pa, e.C, u, v, w,
-                                              e.E, e.qa, true, false, chd::XR_ONE);
+    hipError_t err = e.P.e25_row
+        ? chk::launch_pass_x_e25<T>(e.P.ntask[0], e.P.x_threads, e.P.e25_lds, e.stream, e.d_boxes,
+                                    pa, e.C, u, v, w, e.E, e.qa)
+        : chk::launch_pass_x<T, T>(e.P.mi, e.P.ntask[0], e.P.x_threads, e.P.lds[0], e.stream,
+                                   e.d_boxes, e.P.nbox, pa, e.C, u, v, w, e.E, e.qa, true, false,
+                                   chd::XR_ONE);
     if (e.prof && a && b) {
         (void)hipEventRecord(b, e.stream);
         e.ev_pending.push_back({0, {a, b}});
@@ -1162,7 +1165,7 @@ static ch_status x_program(const chp::Plan& P, int* kind)
 {
     if (!kind) return fail(CH_EINVAL, "null output");
     if (std::isnan(P.dt)) return fail(CH_EINVAL, "no plan yet: step once or pass dt_hint");
-    *kind = P.xseg ? 3 : P.nxl > 1 ? 4 : P.xrow ? (P.xrow_multi ? 2 : 1) : 0;
+    *kind = P.xseg ? 3 : P.nxl > 1 ? 4 : P.xrow ? (P.xrow_multi ? 2 : 1) : P.e25_row ? 1 : 0;
     return CH_OK;
 }
 

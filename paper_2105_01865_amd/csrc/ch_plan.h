@@ -104,6 +104,8 @@ struct Plan {
     double dt = NAN;
     bool acc64 = true;
     bool e25 = false;   // explicit 25-point scheme: no line solves, one row per x task
+    bool e25_row = false;   // ... in its row program (lds[0] stays the general program's)
+    size_t e25_lds = 0;     // LDS of the row program
     bool xrow = false;        // the x pass runs the one-cell-per-thread row program
     bool xrow_multi = false;  // ... with several rows in some task
     int xrm = 0;              // its row mode (chd::XR_ONE, XR_THREAD or XR_WAVE)
@@ -302,7 +304,7 @@ inline ch_status plan_dt(Plan& P, double dt)
     // task, segments of a line balanced.
     bool seg_ok = !P.e25 && P.opt.x_general == 0 && nxm > X_MAX_THREADS;
     for (int b = 0; b < P.nbox && seg_ok; ++b) seg_ok = P.boxes[b].bc[0] == CH_PERIODIC;
-    P.xseg = false;
+    P.xseg = P.e25_row = false;
     if (seg_ok) {
         const int smax = SEG_THREADS - 2 * P.tw_max - 1;
         if (smax >= 64) {
@@ -349,7 +351,7 @@ inline ch_status plan_dt(Plan& P, double dt)
     // the one-row x program: every box's columns feed at most one halo
     // column each (nx >= 6), and every field of every box is under 4 GiB
     // (32-bit byte offsets from one buffer resource per field)
-    bool row_ok = !P.e25 && P.opt.x_general == 0 && P.mi == 1;
+    bool row_ok = P.opt.x_general == 0 && P.mi == 1;
     for (int b = 0; b < P.nbox && row_ok; ++b) {
         const chd::BoxDesc& d = P.boxes[b];
         const double n0 = d.n[0], n1 = d.n[1], n2 = d.n[2], s = (double)sT;
@@ -357,6 +359,12 @@ inline ch_status plan_dt(Plan& P, double dt)
                  (double)d.nf[0] * n1 * n2 * s < 4294967296.0 &&
                  n0 * d.nf[1] * n2 * s < 4294967296.0 && n0 * n1 * d.nf[2] * s < 4294967296.0;
     }
+    // the explicit scheme's row program takes the same boxes, with the tasks
+    // and work-groups of the general one (256^3 FP32: 131 against 207 us per
+    // launch; it is the faster one at every size measured, 64^3 to 256^3)
+    P.e25_row = P.e25 && row_ok;
+    P.e25_lds = chd::x_e25_layout(nxm, (int)sT).total;
+    if (P.e25) row_ok = false;
     auto threads_for = [&](int R) { return ((R * nxm + P.mi - 1) / P.mi + 63) / 64 * 64; };
     // rows per task of box b in the row program with `threads` threads: as
     // many as fill the group, so narrow boxes of an ensemble keep it busy
