@@ -135,9 +135,12 @@ hipError_t launch_press_prep(hipStream_t st, const void* P, void* Pold, void* ph
 template <typename T>
 hipError_t launch_press_rhs(hipStream_t st, const PressArgs& a, const void* C, const void* phat,
                             const void* u, const void* v, const void* w, void* rhs);
+// Spectra are [nz][ny][nxp] complex, nxp >= nx/2 + 1.  sines (periodic z): the
+// tables of launch_press_sines, nx/2 + 1 + ny + nz doubles.
 template <typename T>
 hipError_t launch_press_solve(hipStream_t st, int zwalls, void* spec, void* cp, int nx, int ny,
-                              int nz, double h);
+                              int nz, int nxp, double h, const double* sines);
+hipError_t launch_press_sines(hipStream_t st, double* out, int nx, int ny, int nz);
 template <typename T>
 hipError_t launch_press_update(hipStream_t st, const PressArgs& a, const void* C, const void* P,
                                const void* phat, void* u, void* v, void* w);

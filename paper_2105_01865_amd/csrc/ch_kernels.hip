@@ -1057,13 +1057,18 @@ k_press_rhs(PressArgs a, const T* __restrict__ C, const T* __restrict__ ph,
 // couples the two eliminated halves,
 //   (b_M - c_{M-1}/h^2 - e_{M+1}/h^2) p_M = f_M - (d_{M-1} + g_{M+1})/h^2,
 // and each lane substitutes back over its half.  This halves the serial chain
-// and doubles the threads of the plain Thomas sweep.  The mean mode (lxy = 0)
-// is singular: its mean over z is removed from f, then p[0] = 0 and the rows
-// 0 .. nz-2 give p[1 .. nz-1] by p[k+1] = 2 p[k] - p[k-1] + h^2 f[k]
-// (p[-1] = p[0]), and the mean of p is removed.  Spectra are [nz][ny][nxh]
-// complex (re, im interleaved); cp holds nz x nmodes reals of scratch, of
-// which one per block of PK rows is used.  The result is scaled by `scale`
-// (the inverse transform's 1 / (nx ny)).
+// and doubles the threads of the plain Thomas sweep.  Spectra are [nz][ny][nxp]
+// complex (re, im interleaved, nxp >= nx/2 + 1); cp holds nz x ny x nxp reals of
+// scratch, of which one per block of PK rows is used.  The result is scaled by
+// `scale` (the inverse transform's 1 / (nx ny)).
+//
+// What bounds it: with four waves per SIMD (512^3) each wave's chain of blocks
+// of PK rows, so the next block's loads go out before this block's rows are
+// eliminated.  The mean mode is one serial chain over all of z, its loads
+// behind its stores; it has a work-group of its own (press_mean) that stages z
+// through LDS.  512^3 FP32: 430-439 us against 707 with the mean mode in a lane
+// of a wave and each block's loads after the one before (the spectrum read and
+// written twice at a copy's rate: 440).
 template <typename T>
 struct Cplx;
 template <>
@@ -1075,173 +1080,254 @@ struct Cplx<double> {
     typedef double2 V;
 };
 
+// The mean mode (lxy = 0) of that solve is singular: its mean over z is removed
+// from f, then p[0] = 0 and the rows 0 .. nz-2 give p[1 .. nz-1] by
+// p[k+1] = 2 p[k] - p[k-1] + h^2 f[k] (p[-1] = p[0]), and the mean of p is
+// removed.  One work-group: z goes through LDS in chunks of MEAN_CHUNK rows,
+// thread 0 runs the real parts and thread 1 the imaginary ones.
+constexpr int MEAN_CHUNK = 1024;
+
+template <typename T>
+__device__ void press_mean(T* __restrict__ fs, int64_t s2, int nz, T h2, T sc)
+{
+    __shared__ T sh[2][MEAN_CHUNK];
+    __shared__ T mean[2];
+    const int tid = threadIdx.x, nt = blockDim.x;
+    // f (p) of the chunk's rows into (out of) LDS
+    auto load = [&](int k0, int n) {
+        __syncthreads();
+        for (int e = tid; e < 2 * n; e += nt) sh[e & 1][e >> 1] = fs[(k0 + (e >> 1)) * s2 + (e & 1)];
+        __syncthreads();
+    };
+    constexpr int B = 8;   // rows read ahead of the chain
+    T acc = T(0);
+    for (int k0 = 0; k0 < nz; k0 += MEAN_CHUNK) {
+        const int n = nz - k0 < MEAN_CHUNK ? nz - k0 : MEAN_CHUNK;
+        load(k0, n);
+        if (tid < 2) {
+            int k = 0;
+            for (; k + B <= n; k += B) {
+                T v[B];
+#pragma unroll
+                for (int q = 0; q < B; ++q) v[q] = sh[tid][k + q];
+#pragma unroll
+                for (int q = 0; q < B; ++q) acc += v[q];
+            }
+            for (; k < n; ++k) acc += sh[tid][k];
+        }
+    }
+    const T m = acc / T(nz);
+    T pr = T(0), qr = T(0), sr = T(0);   // p[k-1], p[k], sum of p
+    for (int k0 = 0; k0 < nz; k0 += MEAN_CHUNK) {
+        const int n = nz - k0 < MEAN_CHUNK ? nz - k0 : MEAN_CHUNK;
+        load(k0, n);
+        if (tid < 2) {
+            auto row = [&](int k, T f) {
+                const T fr = f - m;
+                sh[tid][k] = qr;
+                sr += qr;
+                const T lr = k0 + k == 0 ? qr : pr;
+                const T nr = T(2) * qr - lr + h2 * fr;
+                pr = qr;
+                qr = nr;
+            };
+            int k = 0;
+            for (; k + B <= n; k += B) {
+                T v[B];
+#pragma unroll
+                for (int q = 0; q < B; ++q) v[q] = sh[tid][k + q];
+#pragma unroll
+                for (int q = 0; q < B; ++q) row(k + q, v[q]);
+            }
+            for (; k < n; ++k) row(k, sh[tid][k]);
+            if (k0 + n == nz) mean[tid] = sr / T(nz);
+        }
+        __syncthreads();
+        for (int e = tid; e < 2 * n; e += nt) fs[(k0 + (e >> 1)) * s2 + (e & 1)] = sh[e & 1][e >> 1];
+    }
+    __syncthreads();
+    for (int64_t e = tid; e < 2 * (int64_t)nz; e += nt) {
+        T* p = fs + (e >> 1) * s2 + (e & 1);
+        *p = (*p - mean[e & 1]) * sc;
+    }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, double h,
+k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, int nxp, double h,
             double scale)
 {
     typedef typename Cplx<T>::V V;
     const int nxh = nx / 2 + 1;
-    const int64_t nm = (int64_t)ny * nxh;
+    const int64_t nm = (int64_t)ny * nxp;           // complex elements between planes
+    const T sc = T(scale);
+    if (blockIdx.x == 0) {
+        press_mean<T>(spec, 2 * nm, nz, T(h * h), sc);
+        return;
+    }
     const int64_t ngroups = (nm + 31) / 32;
     const double PI = 3.14159265358979323846;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
     const int M = nz / 2;
-    const int len = half == 0 ? M : nz - 1 - M;   // rows eliminated by this lane
+    const int len = half == 0 ? M : nz - 1 - M;     // rows eliminated by this lane
+    const int lmin = nz - 1 - M;                    // ... by the lane with fewer (M or M - 1)
     const T ih2 = T(1.0 / (h * h));
-    const T sc = T(scale);
-    const int64_t st = nm;                          // complex elements between planes
-    constexpr int PK = sizeof(T) == 4 ? 8 : 4;      // planes loaded ahead
-    const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    constexpr int PK = sizeof(T) == 4 ? 8 : 4;      // rows per block
+    const int64_t wave0 = ((int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)(gridDim.x - 1) * blockDim.x) >> 6;
     // the group loop is uniform over a wave: every lane reaches the exchange
     for (int64_t g = wave0; g < ngroups; g += nwaves) {
         const int64_t m = g * 32 + (lane & 31);
-        const bool live = m < nm;
-        const bool special = m == 0;
-        const int64_t mm = live ? m : 0;
-        const int j = (int)(mm / nxh), i = (int)(mm - (int64_t)j * nxh);
+        const int j = (int)(m / nxp), i = (int)(m - (int64_t)j * nxp);
+        const bool on = m < nm && i < nxh && m != 0;   // m = 0 is the mean mode
+        const int64_t mm = on ? m : 0;
         const double sx = sin(PI * i / nx), sy = sin(PI * j / ny);
         const T lxy = T(-4.0 / (h * h) * (sx * sx + sy * sy));
-        V* f = reinterpret_cast<V*>(spec) + mm;       // f[k] at f + k nm
-        auto row = [&](int s) { return half == 0 ? s : nz - 1 - s; };
-        auto diag = [&](int k) { return lxy - (k == 0 || k == nz - 1 ? ih2 : T(2) * ih2); };
+        // row s of the lane's half at f + s * st, its scratch at ck + s * ct
+        const int64_t ct = half == 0 ? nm : -nm, st = ct;
+        V* const fm = reinterpret_cast<V*>(spec) + mm;
+        V* const f = fm + (half == 0 ? 0 : (nz - 1) * nm);
+        T* const ck = cp + mm + (half == 0 ? 0 : (nz - 1) * nm);
+        auto diag = [&](int s) { return lxy - (s == 0 ? ih2 : T(2) * ih2); };   // a half's row s
+        // a block's rows (past the half's end its last row again)
+        auto load = [&](int s0, V* v) {
+            if (s0 + PK <= lmin) {
+                const V* p = f + s0 * st;
+#pragma unroll
+                for (int q = 0; q < PK; ++q) v[q] = p[q * st];
+            } else {
+#pragma unroll
+                for (int q = 0; q < PK; ++q) v[q] = f[(s0 + q < len ? s0 + q : len - 1) * st];
+            }
+        };
         // elimination towards row M in blocks of PK rows: d into f, and into
         // cp at each block's first row the c entering the block (the block's
         // c are formed again from it on the way back)
         T c = T(0), dr = T(0), di = T(0);
-        if (live && !special) {
+        if (on && len > 0) {
+            V nv[PK];
+            load(0, nv);
             for (int s0 = 0; s0 < len; s0 += PK) {
-                cp[row(s0) * nm + m] = c;
+                ck[s0 * ct] = c;
                 V fv[PK];
 #pragma unroll
-                for (int q = 0; q < PK; ++q) fv[q] = f[row(s0 + q < len ? s0 + q : len - 1) * st];
+                for (int q = 0; q < PK; ++q) fv[q] = nv[q];
+                load(s0 + PK < len ? s0 + PK : s0, nv);
 #pragma unroll
                 for (int q = 0; q < PK; ++q) {
                     const int sq = s0 + q;
                     if (sq >= len) break;
-                    const int k = row(sq);
-                    const T den = diag(k) - ih2 * c;
+                    const T den = diag(sq) - ih2 * c;
                     c = ih2 / den;
                     dr = (fv[q].x - ih2 * dr) / den;
                     di = (fv[q].y - ih2 * di) / den;
                     V o;
                     o.x = dr;
                     o.y = di;
-                    f[k * st] = o;
+                    f[sq * st] = o;
                 }
             }
         }
         // row M, read by the lower lane only, and the other half's last
         // coefficients (zero for an empty half), across the wave
         T fmr = T(0), fmi = T(0);
-        if (live && !special && half == 0) {
-            const V v = f[M * st];
+        if (on && half == 0) {
+            const V v = fm[M * nm];
             fmr = v.x;
             fmi = v.y;
         }
         const T oc = __shfl_xor(c, 32), odr = __shfl_xor(dr, 32), odi = __shfl_xor(di, 32);
         const T ofr = __shfl_xor(fmr, 32), ofi = __shfl_xor(fmi, 32);
-        if (live && !special) {
+        if (on) {
             if (half == 1) {
                 fmr = ofr;
                 fmi = ofi;
             }
-            const T den = diag(M) - ih2 * (c + oc);
+            const T dM = lxy - (M == nz - 1 ? ih2 : T(2) * ih2);   // (M > 0 always)
+            const T den = dM - ih2 * (c + oc);
             T xr = (fmr - ih2 * (dr + odr)) / den;
             T xi = (fmi - ih2 * (di + odi)) / den;
             if (half == 0) {
                 V o;
                 o.x = xr * sc;
                 o.y = xi * sc;
-                f[M * st] = o;
+                fm[M * nm] = o;
             }
             // back substitution from row M outwards, block by block: the
             // block's c again from its checkpoint (the same operations as on
             // the way up, so the same values), then its rows in reverse
-            for (int s0 = len > 0 ? (len - 1) / PK * PK : -1; s0 >= 0; s0 -= PK) {
-                V fv[PK];
-                T cc[PK];
-                T cin = cp[row(s0) * nm + m];
+            if (len > 0) {
+                V nv[PK];
+                int s0 = (len - 1) / PK * PK;
+                load(s0, nv);
+                T cnext = ck[s0 * ct];
+                for (; s0 >= 0; s0 -= PK) {
+                    V fv[PK];
+                    T cc[PK];
+                    T cin = cnext;
 #pragma unroll
-                for (int q = 0; q < PK; ++q) fv[q] = f[row(s0 + q < len ? s0 + q : len - 1) * st];
+                    for (int q = 0; q < PK; ++q) fv[q] = nv[q];
+                    const int sn = s0 >= PK ? s0 - PK : 0;
+                    load(sn, nv);
+                    cnext = ck[sn * ct];
 #pragma unroll
-                for (int q = 0; q < PK; ++q) {
-                    cc[q] = T(0);
-                    if (s0 + q >= len) break;
-                    const T den = diag(row(s0 + q)) - ih2 * cin;
-                    cin = ih2 / den;
-                    cc[q] = cin;
+                    for (int q = 0; q < PK; ++q) {
+                        cc[q] = T(0);
+                        if (s0 + q >= len) break;
+                        const T dn = diag(s0 + q) - ih2 * cin;
+                        cin = ih2 / dn;
+                        cc[q] = cin;
+                    }
+#pragma unroll
+                    for (int q = PK - 1; q >= 0; --q) {
+                        const int sq = s0 + q;
+                        if (sq >= len) continue;
+                        xr = fv[q].x - cc[q] * xr;
+                        xi = fv[q].y - cc[q] * xi;
+                        V o;
+                        o.x = xr * sc;
+                        o.y = xi * sc;
+                        f[sq * st] = o;
+                    }
                 }
-#pragma unroll
-                for (int q = PK - 1; q >= 0; --q) {
-                    const int sq = s0 + q;
-                    if (sq >= len) continue;
-                    xr = fv[q].x - cc[q] * xr;
-                    xi = fv[q].y - cc[q] * xi;
-                    V o;
-                    o.x = xr * sc;
-                    o.y = xi * sc;
-                    f[row(sq) * st] = o;
-                }
-            }
-        }
-        if (live && special && half == 0) {
-            T* fs = spec;                  // mode 0: f[k] at fs + 2 k nm
-            const int64_t s2 = 2 * nm;
-            T mr = T(0), mi = T(0);
-            for (int k = 0; k < nz; ++k) {
-                mr += fs[k * s2];
-                mi += fs[k * s2 + 1];
-            }
-            mr /= T(nz);
-            mi /= T(nz);
-            const T h2 = T(h * h);
-            T pr = T(0), pi = T(0), qr = T(0), qi = T(0);   // p[k-1], p[k]
-            T sr = T(0), si = T(0);
-            for (int k = 0; k < nz; ++k) {
-                const T fr = fs[k * s2] - mr, fi = fs[k * s2 + 1] - mi;
-                fs[k * s2] = qr;         // p[k]
-                fs[k * s2 + 1] = qi;
-                sr += qr;
-                si += qi;
-                const T lr = k == 0 ? qr : pr, li = k == 0 ? qi : pi;
-                const T nr = T(2) * qr - lr + h2 * fr, ni = T(2) * qi - li + h2 * fi;
-                pr = qr;
-                pi = qi;
-                qr = nr;
-                qi = ni;
-            }
-            sr /= T(nz);
-            si /= T(nz);
-            for (int k = 0; k < nz; ++k) {
-                fs[k * s2] = (fs[k * s2] - sr) * sc;
-                fs[k * s2 + 1] = (fs[k * s2 + 1] - si) * sc;
             }
         }
     }
 }
 
-// Periodic z: divide the 3-D spectrum [nz][ny][nxh] by the eigenvalue of the
-// 7-point Laplacian, zero mode to 0, scaled by 1 / (nx ny nz).
+// sin(pi i / n), i < count: the eigenvalue tables of the periodic solve, made
+// once per mesh.
+__global__ void __launch_bounds__(256) k_press_sines(double* __restrict__ out, int n, int count)
+{
+    const double PI = 3.14159265358979323846;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) out[i] = sin(PI * i / n);
+}
+
+// Periodic z: divide the 3-D spectrum [nz][ny][nxp] by the eigenvalue of the
+// 7-point Laplacian, zero mode to 0, scaled by 1 / (nx ny nz).  The sines come
+// from the tables tx, ty, tz: with three double-precision sines per element the
+// pass was compute-bound (240 x 180 x 160 FP64: 21 us now, 40 then).
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_press_div(T* __restrict__ spec, int nx, int ny, int nz, double h, double scale)
+k_press_div(T* __restrict__ spec, int nx, int ny, int nz, int nxp, double h, double scale,
+            const double* __restrict__ tx, const double* __restrict__ ty,
+            const double* __restrict__ tz)
 {
-    const int nxh = nx / 2 + 1;
-    const int64_t n = (int64_t)nz * ny * nxh;
-    const double PI = 3.14159265358979323846;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(e % nxh);
-        const int64_t r = e / nxh;
-        const int j = (int)(r % ny), k = (int)(r / ny);
-        const double sx = sin(PI * i / nx), sy = sin(PI * j / ny), sz = sin(PI * k / nz);
+    typedef typename Cplx<T>::V V;
+    const uint32_t nxh = nx / 2 + 1;
+    const uint32_t n = (uint32_t)nz * ny * nxh;   // fewer than 2^31 cells
+    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
+        const uint32_t r = e / nxh, i = e - r * nxh, k = r / ny, j = r - k * ny;
+        const double sx = tx[i], sy = ty[j], sz = tz[k];
         const double lam = -4.0 / (h * h) * (sx * sx + sy * sy + sz * sz);
         const T f = (e == 0) ? T(0) : T(scale / lam);
-        spec[2 * e] *= f;
-        spec[2 * e + 1] *= f;
+        V* p = reinterpret_cast<V*>(spec) + ((int64_t)r * nxp + i);
+        V v = *p;
+        v.x *= f;
+        v.y *= f;
+        *p = v;
     }
 }
 
@@ -1590,19 +1676,33 @@ hipError_t launch_press_rhs(hipStream_t st, const PressArgs& a, const void* C, c
 
 template <typename T>
 hipError_t launch_press_solve(hipStream_t st, int zwalls, void* spec, void* cp, int nx, int ny,
-                              int nz, double h)
+                              int nz, int nxp, double h, const double* sines)
 {
     if (zwalls) {
-        // one wave per 32 modes (two lanes per mode)
-        const int64_t nm = (int64_t)ny * (nx / 2 + 1);
-        hipLaunchKernelGGL((k_press_tri<T>), dim3(grid_for((nm + 31) / 32 * 64)), dim3(256), 0, st,
-                           (T*)spec, (T*)cp, nx, ny, nz, h, 1.0 / ((double)nx * ny));
+        // one work-group for the mean mode, one wave per 32 modes (two lanes per mode)
+        const int64_t nm = (int64_t)ny * nxp;
+        hipLaunchKernelGGL((k_press_tri<T>), dim3(grid_for((nm + 31) / 32 * 64) + 1), dim3(256), 0,
+                           st, (T*)spec, (T*)cp, nx, ny, nz, nxp, h, 1.0 / ((double)nx * ny));
     } else {
         const int64_t n = (int64_t)nz * ny * (nx / 2 + 1);
+        const double* sy = sines + (nx / 2 + 1);
         hipLaunchKernelGGL((k_press_div<T>), dim3(grid_for(n)), dim3(256), 0, st, (T*)spec, nx,
-                           ny, nz, h, 1.0 / ((double)nx * ny * nz));
+                           ny, nz, nxp, h, 1.0 / ((double)nx * ny * nz), sines, sy, sy + ny);
     }
     return hipGetLastError();
+}
+
+hipError_t launch_press_sines(hipStream_t st, double* out, int nx, int ny, int nz)
+{
+    const int n[3] = {nx, ny, nz}, count[3] = {nx / 2 + 1, ny, nz};
+    for (int d = 0; d < 3; ++d) {
+        hipLaunchKernelGGL(k_press_sines, dim3(grid_for(count[d])), dim3(256), 0, st, out, n[d],
+                           count[d]);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        out += count[d];
+    }
+    return hipSuccess;
 }
 
 template <typename T>
@@ -1671,13 +1771,15 @@ template hipError_t launch_scan<float>(hipStream_t, int, void*, const void*, int
 template hipError_t launch_press_prep<double>(hipStream_t, const void*, void*, void*, int64_t);
 template hipError_t launch_press_rhs<double>(hipStream_t, const PressArgs&, const void*, const void*,
                                           const void*, const void*, const void*, void*);
-template hipError_t launch_press_solve<double>(hipStream_t, int, void*, void*, int, int, int, double);
+template hipError_t launch_press_solve<double>(hipStream_t, int, void*, void*, int, int, int, int,
+                                               double, const double*);
 template hipError_t launch_press_update<double>(hipStream_t, const PressArgs&, const void*,
                                              const void*, const void*, void*, void*, void*);
 template hipError_t launch_press_prep<float>(hipStream_t, const void*, void*, void*, int64_t);
 template hipError_t launch_press_rhs<float>(hipStream_t, const PressArgs&, const void*, const void*,
                                           const void*, const void*, const void*, void*);
-template hipError_t launch_press_solve<float>(hipStream_t, int, void*, void*, int, int, int, double);
+template hipError_t launch_press_solve<float>(hipStream_t, int, void*, void*, int, int, int, int,
+                                              double, const double*);
 template hipError_t launch_press_update<float>(hipStream_t, const PressArgs&, const void*,
                                              const void*, const void*, void*, void*, void*);
 
