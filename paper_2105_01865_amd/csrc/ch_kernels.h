@@ -58,6 +58,11 @@ hipError_t launch_check_velocity(hipStream_t st, const chd::BoxDesc* boxes, int 
 // of every 4 consecutive targets 4t .. 4t+3 lie within the 6 cyclically
 // consecutive coarse points starting at target 4t's first tap.  Weights of
 // the y and z stencils are in the working precision.
+constexpr int MARCH_BAND = 8;   // target rows of a sub-band of the marching kernel
+// Where the taps of consecutive targets start, within groups of 4 in x and
+// MARCH_BAND in y: anywhere, at 0 0 1 1 .., or at 0 1 1 2 ..
+enum { MARCH_ANY = 0, MARCH_FACE = 1, MARCH_CENTRE = 2 };
+
 struct InterpArgs {
     const void* src;        // coarse component [.][sy][sx]
     void* dst;              // target [tnz][tny][tnx]
@@ -75,6 +80,14 @@ struct InterpArgs {
     const int* iz;          // 4 taps per target plane, z
     const void* wz;
     const int* band;
+    // the marching kernel (rm > 0): coarse rows held per thread (8 or 11), first
+    // y tap of each target row, threads per sub-band of 8 target rows (a
+    // multiple of 64), sub-bands per group, bands of groups, chunks of kc target
+    // planes
+    int rm, xp, yp;
+    const int* iy0;
+    int sxw, nsub, nband, nchunk, kc;
+    int nt;                 // non-temporal stores
 };
 
 // LDS of one transfer work-group: rmax coarse rows and jb target rows

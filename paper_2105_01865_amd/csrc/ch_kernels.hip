@@ -274,7 +274,7 @@ k_check_velocity(const chd::BoxDesc* __restrict__ boxes, int nbox, const T* __re
 // streaming it out leaves them to the coarse rows, which are read again);
 // the coarse data is read through the caches about (rows per band / band
 // height) times per target plane.
-template <typename T, int JB, int MA, bool PIPE>
+template <typename T, int JB, int MA>
 __global__ void __launch_bounds__(256)
 k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
          const int* __restrict__ band, const int* __restrict__ izt, const T* __restrict__ wzt,
@@ -327,33 +327,6 @@ k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
     const int per = (items + a.nwg - 1) / a.nwg;
     const int it0 = xcd_task(blockIdx.x, a.nwg) * per;
     const int it1 = it0 + per < items ? it0 + per : items;
-    // PIPE (one batch of loads covers an item: the coarse row fits the group
-    // and no band is taller than the rows in flight): the next item's coarse
-    // rows are loaded while this item's targets are stored, issued before
-    // phase C and combined into LDS at the top of the next item.
-    constexpr bool pipe = PIPE;
-    T vp[PIPE ? MA : 1][4];
-    auto issue = [&](int item) {   // the item's coarse rows at column tid
-        if constexpr (!PIPE) return;
-        const int b = item / a.tnz, k = item - b * a.tnz;
-        const int base = band[2 * b], span = band[2 * b + 1];
-        const chd::PlaneRef<T> p0(src + (int64_t)izt[4 * k] * a.plane, pbytes);
-        const chd::PlaneRef<T> p1(src + (int64_t)izt[4 * k + 1] * a.plane, pbytes);
-        const chd::PlaneRef<T> p2(src + (int64_t)izt[4 * k + 2] * a.plane, pbytes);
-        const chd::PlaneRef<T> p3(src + (int64_t)izt[4 * k + 3] * a.plane, pbytes);
-        const int cx = tid < sx ? tid : 0;
-#pragma unroll
-        for (int m = 0; m < (PIPE ? MA : 1); ++m) {
-            int rr = base + m;
-            if (rr >= a.sy) rr -= a.sy;
-            const uint32_t boff = (uint32_t)((m < span ? rr * sx + cx : cx) * (int)sizeof(T));
-            vp[m][0] = p0(boff);
-            vp[m][1] = p1(boff);
-            vp[m][2] = p2(boff);
-            vp[m][3] = p3(boff);
-        }
-    };
-    if (pipe && it0 < it1) issue(it0);
     for (int item = it0; item < it1; ++item) {
         const int b = item / a.tnz, k = item - b * a.tnz;
         const int j0 = b * JB;
@@ -361,15 +334,7 @@ k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
         const int base = band[2 * b], span = band[2 * b + 1];
         __syncthreads();   // the previous item's readers are done with the LDS
         // A: coarse rows base .. base + span - 1 (cyclic), z stencil applied
-        if constexpr (PIPE) {
-            const T w0 = wzt[4 * k], w1 = wzt[4 * k + 1], w2 = wzt[4 * k + 2], w3 = wzt[4 * k + 3];
-            if (tid < sx)
-#pragma unroll
-                for (int m = 0; m < (PIPE ? MA : 1); ++m)
-                    if (m < span)
-                        zr[m * sx + tid] =
-                            ((w0 * vp[m][0] + w1 * vp[m][1]) + w2 * vp[m][2]) + w3 * vp[m][3];
-        } else {
+        {
             const chd::PlaneRef<T> p0(src + (int64_t)izt[4 * k] * a.plane, pbytes);
             const chd::PlaneRef<T> p1(src + (int64_t)izt[4 * k + 1] * a.plane, pbytes);
             const chd::PlaneRef<T> p2(src + (int64_t)izt[4 * k + 2] * a.plane, pbytes);
@@ -410,7 +375,6 @@ k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
             }
         }
         __syncthreads();
-        if (pipe && item + 1 < it1) issue(item + 1);
         // C: x stencil, every target point written once
         T* out = dst + ((int64_t)k * a.tny + j0) * a.tnx;
         if (win) {
@@ -446,6 +410,204 @@ k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
                     for (int t = 0; t < 4; ++t) acc += T(wxt[4 * i + t]) * row[ixt[4 * i + t]];
                     __builtin_nontemporal_store(acc, out + (int64_t)jj * a.tnx + i);
                 }
+        }
+    }
+}
+
+// The same transfer for upsampling in y with coarse rows of at most 256 points
+// (MARCH_ROWS consecutive target rows span at most RM coarse rows, whose taps
+// are consecutive; the x taps of 4 targets lie in 6 points).  A work-group
+// takes a band of target rows and marches up through kc target planes.  Its
+// waves are split into sub-bands of MARCH_ROWS rows; a thread owns one coarse
+// column of its sub-band and keeps the RM rows of the item's four coarse planes
+// in registers: the z stencil, then the y stencil are formed there, so only the
+// target rows on the coarse columns go through LDS (two buffers, one barrier
+// per plane).  The next plane's loads go out before this plane's x stencil, and
+// not at all where it reads the same four coarse planes.
+//
+// XP and YP say where the taps of neighbouring targets start: at two fine cells
+// per coarse one the first taps of consecutive targets are 0 0 1 1 (MARCH_FACE:
+// faces on faces) or 0 1 1 2 (MARCH_CENTRE: centres on centres) in every group,
+// so each target takes its four taps with no selection; MARCH_ANY selects (a
+// 4 x 6 matrix in x, the row among RM - 3 in y).
+//
+// What bounds it: the stencils' VALU work and the groups' chains of loads,
+// barrier and stores; the stores alone take 90 us at 512^3 FP32.  Per component,
+// caches cold, against the general kernel (three barriers and scalar loads of
+// the y stencil per item, the z stencil's rows through LDS): 512^3 FP32 169-182
+// against 202 us, FP64 331-340 against 379-383, 256^3 FP32 34 against 76, FP64
+// 54 against 114.
+constexpr int MARCH_ROWS = MARCH_BAND;
+// first tap of target q in its group
+template <int P>
+constexpr int march_tap(int q)
+{
+    return P == MARCH_FACE ? q / 2 : (q + 1) / 2;
+}
+
+template <typename T, int RM, int XP, int YP>
+__global__ void __launch_bounds__(256)
+k_interp_march(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
+               const int* __restrict__ iy0, const int* __restrict__ izt,
+               const T* __restrict__ wzt, const T* __restrict__ wyt,
+               const int* __restrict__ ixt, const double* __restrict__ wxt)
+{
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    constexpr int XQ = 4, MR = MARCH_ROWS;
+    constexpr int NW = XP == MARCH_ANY ? 6 : march_tap<XP>(XQ - 1) + 4;   // points of 4 targets
+    constexpr int NX = XP == MARCH_ANY ? NW : 4;                          // weights of a target
+    extern __shared__ __align__(16) unsigned char smem[];
+    T* yr = reinterpret_cast<T*>(smem);   // 2 x (nsub MR) x sx
+    constexpr uint32_t sT = sizeof(T);
+    const int sx = a.sx, nsub = a.nsub, nt = 256;
+    const int tid = threadIdx.x;
+    const uint32_t pbytes = (uint32_t)(a.plane * sizeof(T));
+    const int wg = xcd_task(blockIdx.x, gridDim.x);
+    const int bandi = wg / a.nchunk, chunk = wg - bandi * a.nchunk;
+    const int k0 = chunk * a.kc, k1 = k0 + a.kc < a.tnz ? k0 + a.kc : a.tnz;
+    const int j0 = bandi * MR * nsub;                          // the group's target rows
+    const int njw = a.tny - j0 < MR * nsub ? a.tny - j0 : MR * nsub;
+    const int bufsz = MR * nsub * sx;
+
+    // y stencil of this wave's sub-band: coarse rows base, base + 1, ... (cyclic),
+    // the taps of target row jj from row l[jj] of them on
+    const int sub = chd::uniform_i(tid / a.sxw);
+    const int js = j0 + MR * sub;
+    const bool wact = sub < nsub && js < a.tny;
+    const int cx = tid - sub * a.sxw;
+    const bool cact = wact && cx < sx;
+    const int jb = wact ? js : 0;
+    const int base = iy0[jb];
+    uint32_t roff[RM];   // byte offset of coarse row base + r
+#pragma unroll
+    for (int r = 0; r < RM; ++r) roff[r] = (uint32_t)((base + r) % a.sy * sx) * sT;
+    const uint32_t xb = (uint32_t)(cact ? cx : 0) * sT;
+
+    T vp[RM][4];
+    auto issue = [&](int k) {
+        const chd::PlaneRef<T> p0(src + (int64_t)izt[4 * k] * a.plane, pbytes);
+        const chd::PlaneRef<T> p1(src + (int64_t)izt[4 * k + 1] * a.plane, pbytes);
+        const chd::PlaneRef<T> p2(src + (int64_t)izt[4 * k + 2] * a.plane, pbytes);
+        const chd::PlaneRef<T> p3(src + (int64_t)izt[4 * k + 3] * a.plane, pbytes);
+#pragma unroll
+        for (int r = 0; r < RM; ++r) {
+            vp[r][0] = p0(xb, roff[r]);
+            vp[r][1] = p1(xb, roff[r]);
+            vp[r][2] = p2(xb, roff[r]);
+            vp[r][3] = p3(xb, roff[r]);
+        }
+    };
+    issue(k0);
+
+    int l[MR];
+    T wy[MR][4];
+#pragma unroll
+    for (int jj = 0; jj < MR; ++jj) {
+        const int j = jb + jj < a.tny ? jb + jj : a.tny - 1;
+        if constexpr (YP == MARCH_ANY) {
+            int d = iy0[j] - base;
+            if (d < 0) d += a.sy;
+            l[jj] = d;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wy[jj][t] = wyt[4 * j + t];
+    }
+
+    // x stencil of this thread: targets xi0 .. xi0 + 3 of rows rg0 (mod rgs) from
+    // the NW points from ws on.  The table reads are unconditional (a target
+    // past the end repeats the last one), so that they go out together.
+    const int tc = (a.tnx + XQ - 1) / XQ;
+    const int rgs = nt / tc, rg0 = tid / tc;
+    const int xi0 = XQ * (tid - rg0 * tc);
+    const bool xact = rg0 < rgs;
+    const bool vec = (a.tnx % XQ) == 0 && (reinterpret_cast<uintptr_t>(dst) % sizeof(T4)) == 0;
+    const int ws = ixt[4 * xi0];
+    int woff[NW];
+#pragma unroll
+    for (int n = 0; n < NW; ++n) woff[n] = (ws + n) % sx;
+    T M[XQ][NX];
+#pragma unroll
+    for (int q = 0; q < XQ; ++q) {
+        const int i = xi0 + q < a.tnx ? xi0 + q : a.tnx - 1;
+        if constexpr (XP == MARCH_ANY) {
+#pragma unroll
+            for (int n = 0; n < NX; ++n) M[q][n] = T(0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                int d = ixt[4 * i + t] - ws;
+                if (d < 0) d += sx;
+                const T w = T(wxt[4 * i + t]);
+#pragma unroll
+                for (int n = 0; n < NX; ++n) M[q][n] += d == n ? w : T(0);
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) M[q][t] = T(wxt[4 * i + t]);
+        }
+    }
+
+    for (int k = k0; k < k1; ++k) {
+        T* buf = yr + ((k - k0) & 1) * bufsz;
+        {
+            const T w0 = wzt[4 * k], w1 = wzt[4 * k + 1], w2 = wzt[4 * k + 2], w3 = wzt[4 * k + 3];
+            T zc[RM];
+#pragma unroll
+            for (int r = 0; r < RM; ++r)
+                zc[r] = ((w0 * vp[r][0] + w1 * vp[r][1]) + w2 * vp[r][2]) + w3 * vp[r][3];
+            T* out = buf + MR * sub * sx + cx;
+#pragma unroll
+            for (int jj = 0; jj < MR; ++jj) {
+                auto comb = [&](int c) {
+                    return ((wy[jj][0] * zc[c] + wy[jj][1] * zc[c + 1]) + wy[jj][2] * zc[c + 2]) +
+                           wy[jj][3] * zc[c + 3];
+                };
+                T o = T(0);
+                if constexpr (YP == MARCH_ANY) {
+                    // the taps start at most one row later per target row
+#pragma unroll
+                    for (int c = 0; c <= (jj < RM - 4 ? jj : RM - 4); ++c)
+                        if (l[jj] == c) o = comb(c);
+                } else {
+                    o = comb(march_tap<YP>(jj));
+                }
+                if (cact && js + jj < a.tny) out[jj * sx] = o;
+            }
+        }
+        __syncthreads();
+        if (k + 1 < k1) {
+            const int* z0 = izt + 4 * k;
+            if (z0[4] != z0[0] || z0[5] != z0[1] || z0[6] != z0[2] || z0[7] != z0[3]) issue(k + 1);
+        }
+        // x stencil, every target point written once
+        if (xact) {
+            T* out = dst + ((int64_t)k * a.tny + j0) * a.tnx + xi0;
+            for (int jj = rg0; jj < njw; jj += rgs) {
+                const T* row = buf + jj * sx;
+                T p[NW];
+#pragma unroll
+                for (int n = 0; n < NW; ++n) p[n] = row[woff[n]];
+                T y[XQ];
+#pragma unroll
+                for (int q = 0; q < XQ; ++q) {
+                    const int c = XP == MARCH_ANY ? 0 : march_tap<XP>(q);
+                    T acc = M[q][0] * p[c];
+#pragma unroll
+                    for (int n = 1; n < NX; ++n) acc += M[q][n] * p[c + n];
+                    y[q] = acc;
+                }
+                T* o = out + (int64_t)jj * a.tnx;
+                if (vec) {
+                    if (a.nt)
+                        __builtin_nontemporal_store(T4{y[0], y[1], y[2], y[3]},
+                                                    reinterpret_cast<T4*>(o));
+                    else
+                        *reinterpret_cast<T4*>(o) = T4{y[0], y[1], y[2], y[3]};
+                } else {
+#pragma unroll
+                    for (int q = 0; q < XQ; ++q)
+                        if (xi0 + q < a.tnx) o[q] = y[q];
+                }
+            }
         }
     }
 }
@@ -1556,34 +1718,46 @@ hipError_t launch_check_velocity(hipStream_t st, const chd::BoxDesc* boxes, int 
     return hipGetLastError();
 }
 
-template <typename T, int JB, int MA, bool PIPE>
-static hipError_t launch_interp_k(hipStream_t st, const InterpArgs& a)
-{
-    if (a.lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)&k_interp<T, JB, MA, PIPE>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)a.lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL((k_interp<T, JB, MA, PIPE>), dim3((unsigned)a.nwg), dim3(256), a.lds, st,
-                       a, (const T*)a.src, (T*)a.dst, a.band, a.iz, (const T*)a.wz, a.ly,
-                       (const T*)a.wy, a.ix, a.wx);
-    return hipGetLastError();
-}
-
 template <typename T, int JB>
 static hipError_t launch_interp_jb(hipStream_t st, const InterpArgs& a)
 {
     constexpr int MA = sizeof(T) == 4 ? 20 : 12;  // rows of loads in flight
-    // one batch of loads per item: coarse rows of at most 256 points, bands
-    // of at most MA rows
-    if (a.rmax <= MA && a.sx <= 256) return launch_interp_k<T, JB, MA, true>(st, a);
-    return launch_interp_k<T, JB, MA, false>(st, a);
+    if (a.lds > 65536) {
+        hipError_t e = hipFuncSetAttribute((const void*)&k_interp<T, JB, MA>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)a.lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_interp<T, JB, MA>), dim3((unsigned)a.nwg), dim3(256), a.lds, st, a,
+                       (const T*)a.src, (T*)a.dst, a.band, a.iz, (const T*)a.wz, a.ly,
+                       (const T*)a.wy, a.ix, a.wx);
+    return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_interp(hipStream_t st, const InterpArgs& a)
 {
+    if (a.rm) {
+        const dim3 grid((unsigned)(a.nband * a.nchunk));
+        const size_t lds = (size_t)2 * MARCH_ROWS * a.nsub * a.sx * sizeof(T);
+        auto go = [&](auto rm, auto xp, auto yp) {
+            hipLaunchKernelGGL((k_interp_march<T, decltype(rm)::value, decltype(xp)::value,
+                                               decltype(yp)::value>),
+                               grid, dim3(256), lds, st, a, (const T*)a.src, (T*)a.dst, a.iy0, a.iz,
+                               (const T*)a.wz, (const T*)a.wy, a.ix, a.wx);
+            return hipGetLastError();
+        };
+        using chd::IC;
+        constexpr IC<MARCH_ANY> any{};
+        constexpr IC<MARCH_FACE> face{};
+        constexpr IC<MARCH_CENTRE> centre{};
+        if (a.xp == MARCH_FACE && a.yp == MARCH_CENTRE) return go(IC<8>{}, face, centre);
+        if (a.xp == MARCH_CENTRE && a.yp == MARCH_FACE) return go(IC<7>{}, centre, face);
+        if (a.xp == MARCH_CENTRE && a.yp == MARCH_CENTRE) return go(IC<8>{}, centre, centre);
+        if (a.rm == 8) return go(IC<8>{}, any, any);
+        if (a.rm == 11) return go(IC<11>{}, any, any);
+        return hipErrorInvalidValue;
+    }
     switch (a.jb) {
     case 32: return launch_interp_jb<T, 32>(st, a);
     case 16: return launch_interp_jb<T, 16>(st, a);

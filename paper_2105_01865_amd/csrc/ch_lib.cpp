@@ -366,6 +366,10 @@ struct Transfer {
     void* wy = nullptr;
     void* wz = nullptr;
     bool ok = false;   // built (a source row too long for the LDS leaves it unbuilt)
+    // the marching kernel: coarse rows per thread (0: not taken) and the first y
+    // tap of each target row
+    int rm = 0, xp = 0, yp = 0;
+    int* iy0 = nullptr;
 };
 
 // Transfers of one handle: the plain transfer of u, v, w; the fine cell
@@ -406,10 +410,10 @@ void free_transfer(Transfer& t)
         t.idx[a] = nullptr;
         t.wt[a] = nullptr;
     }
-    void* p[4] = {t.band, t.ly, t.wy, t.wz};
+    void* p[5] = {t.band, t.ly, t.wy, t.wz, t.iy0};
     for (void* q : p)
         if (q) (void)hipFree(q);
-    t.band = t.ly = nullptr;
+    t.band = t.ly = t.iy0 = nullptr;
     t.wy = t.wz = nullptr;
     t.ok = false;
 }
@@ -498,6 +502,59 @@ bool interp_xwin(const std::vector<int>& ix, int64_t tnx, int sx)
     return true;
 }
 
+// Most work-groups of a marching transfer (beyond, its groups march further):
+// whole rounds of those resident (6 per CU in single precision, 3 in double),
+// two and eight.  512^3, us per component: FP32 1024 groups 199, 2048 181, 3008
+// 169, 3328 182, 8192 184; FP64 2048 423, 4096 345, 6144 331, 8192 328.
+template <typename T>
+constexpr int64_t march_wg()
+{
+    return sizeof(T) == 4 ? 3072 : 6144;
+}
+// Single-precision targets from this size on are stored non-temporally: they
+// are out of the caches before anything reads them (512^3 181 against 187 us).
+// Below, the step or the integration that follows reads them from the caches,
+// and in double precision a lane's 32 bytes are two half-line stores that only
+// a cache joins (256^3 FP64 54 against 63 us, with the integration 112 against
+// 140).
+constexpr int64_t MARCH_NT_BYTES = 256ll << 20;
+
+// Coarse rows a thread of the marching transfer holds (8 or 11), or 0 where it
+// does not apply: coarse rows of at most 256 points, at most 1024 targets in x
+// whose taps lie in 6-point windows, and in every 8 target rows from a multiple
+// of 8 on consecutive y taps that start at most one coarse row later per row.
+int interp_march_rows(const std::vector<int>& iy, int64_t tnx, int64_t tny, int sx, int sy, int xwin)
+{
+    if (sx > 256 || tnx > 1024 || !xwin || sy < 4) return 0;
+    int span = 0;
+    for (int64_t j = 0; j < tny; ++j) {
+        const int64_t jb = j / chk::MARCH_BAND * chk::MARCH_BAND;
+        for (int q = 1; q < 4; ++q)
+            if (iy[4 * j + q] != (iy[4 * j] + q) % sy) return 0;
+        const int l = (iy[4 * j] - iy[4 * jb] + sy) % sy;
+        const int prev = j == jb ? 0 : (iy[4 * (j - 1)] - iy[4 * jb] + sy) % sy;
+        if (l < prev || l > prev + 1) return 0;
+        span = std::max(span, l + 4);
+    }
+    return span <= 8 ? 8 : span <= 11 ? 11 : 0;
+}
+
+// The pattern (chk::MARCH_*) of the targets' first taps in groups of `group`,
+// each target's taps consecutive.
+int interp_pattern(const std::vector<int>& ix, int64_t tn, int n, int group)
+{
+    bool face = true, centre = true;
+    for (int64_t i = 0; i < tn; ++i) {
+        for (int q = 1; q < 4; ++q)
+            if (ix[4 * i + q] != (ix[4 * i] + q) % n) return chk::MARCH_ANY;
+        const int g = (int)(i % group);
+        const int d = (ix[4 * i] - ix[4 * (i - g)] + n) % n;
+        face = face && d == g / 2;
+        centre = centre && d == (g + 1) / 2;
+    }
+    return face ? chk::MARCH_FACE : centre ? chk::MARCH_CENTRE : chk::MARCH_ANY;
+}
+
 template <typename T>
 hipError_t launch_transfer(const Transfer& t, hipStream_t st, const void* src, void* dst)
 {
@@ -523,6 +580,22 @@ hipError_t launch_transfer(const Transfer& t, hipStream_t st, const void* src, v
     ia.iz = t.idx[2];
     ia.wz = t.wz;
     ia.band = t.band;
+    ia.rm = t.rm;
+    ia.xp = t.xp;
+    ia.yp = t.yp;
+    ia.iy0 = t.iy0;
+    if (t.rm) {
+        // a wave's columns belong to one sub-band; planes per group so that the
+        // chip has a few groups per CU, at least 4 to reuse the stencils
+        ia.sxw = (ia.sx + 63) / 64 * 64;
+        ia.nsub = std::max(1, 256 / ia.sxw);
+        const int rows = chk::MARCH_BAND * ia.nsub;
+        ia.nband = (ia.tny + rows - 1) / rows;
+        ia.kc = std::max(4, (int)(((int64_t)ia.tnz * ia.nband + march_wg<T>() - 1) / march_wg<T>()));
+        ia.kc = std::min(ia.kc, ia.tnz);
+        ia.nchunk = (ia.tnz + ia.kc - 1) / ia.kc;
+        ia.nt = sizeof(T) == 4 && t.tn[0] * t.tn[1] * t.tn[2] * (int64_t)sizeof(T) >= MARCH_NT_BYTES;
+    }
     return chk::launch_interp<T>(st, ia);
 }
 
@@ -942,12 +1015,18 @@ ch_status build_transfer(Transfer& t, const chp::SrcAxis* const src[3],
         ly[q] = (int)(((idx[1][q] - base + sy) % sy) * sx);
     }
     t.xwin = interp_xwin(idx[0], t.tn[0], (int)sx) ? 1 : 0;
+    t.rm = interp_march_rows(idx[1], t.tn[0], t.tn[1], (int)sx, (int)sy, t.xwin);
+    t.xp = interp_pattern(idx[0], t.tn[0], (int)sx, 4);
+    t.yp = interp_pattern(idx[1], t.tn[1], (int)sy, chk::MARCH_BAND);
+    std::vector<int> iy0;
+    for (int64_t j = 0; j < t.tn[1]; ++j) iy0.push_back(idx[1][4 * j]);
     bool good = true;
     for (int a = 0; a < 3 && good; a += 2)
         good = upload((void**)&t.idx[a], idx[a].data(), sizeof(int) * idx[a].size()) &&
                upload((void**)&t.wt[a], wt[a].data(), sizeof(double) * wt[a].size());
     good = good && upload((void**)&t.band, band.data(), sizeof(int) * band.size()) &&
            upload((void**)&t.ly, ly.data(), sizeof(int) * ly.size()) &&
+           upload((void**)&t.iy0, iy0.data(), sizeof(int) * iy0.size()) &&
            upload_weights(&t.wy, wt[1], precision) && upload_weights(&t.wz, wt[2], precision);
     if (!good) {
         free_transfer(t);
