@@ -481,6 +481,30 @@ inline ch_status plan_dt(Plan& P, double dt)
         // that allows (each task reloads 6 planes to start its march)
         const int64_t rows_total = cells / std::max(1, nxm);
         zc = (int)std::max<int64_t>(1, std::min<int64_t>(16, rows_total / R / 2048));
+        if (row_ok && zc <= 12) {
+            // the row program marches up to 12 planes to come down to the
+            // threads of 1024 groups of 256: 2048 groups prime and solve too
+            // often (per step, 96^3 FP64 142 -> 129 us, 80^3 120 -> 110, 300 x
+            // 100 x 50 FP32 169 -> 144, 128^3 135 -> 130); of the five counts
+            // down from there, a single box takes the one whose fullest CU has
+            // least to do, a task costing its planes and 2.5 more (152 x 235 x
+            // 89 FP64: 12 planes 322 us, 10 planes 313)
+            const int64_t target = 1024 * 256 / std::max(64, P.x_threads);
+            const int zn = (int)std::max<int64_t>(1, std::min<int64_t>(12, (rows_total / R + target / 2) / target));
+            zc = std::max(zc, zn);
+            if (P.nbox == 1) {
+                const int64_t nyb = (P.boxes[0].n[1] + R - 1) / R, nz = P.boxes[0].n[2];
+                double best = INFINITY;
+                for (int z = zn; z >= std::max(1, zn - 4); --z) {
+                    const int64_t tasks = nyb * ((nz + z - 1) / z);
+                    const double cost = (double)((tasks + 255) / 256) * (z + 2.5);
+                    if (cost < best) {
+                        best = cost;
+                        zc = z;
+                    }
+                }
+            }
+        }
         zc = std::min(zc, zlim);
         while (zc > 1 && !lds_fits(zc, false)) --zc;
     }
