@@ -64,6 +64,8 @@ struct BoxDesc {
     double a1[3], a2[3], ic[3];   // line-solve recurrences (ic = 1/c)
     int32_t tw[3];      // warm-up length of the recurrences
     int32_t seg[2];     // segment length of the y and z passes
+    int32_t segk[2];    // > 0: the chunk length of the whole line, of which the
+                        // segments are multiples (seg_chunk)
     int32_t task0[3];   // first global task of this box in passes x, y, z
     int32_t ntask[3];   // tasks of this box in passes x, y, z
     int32_t mblk0;      // first mass block of this box
@@ -470,6 +472,22 @@ CH_HD Chunk line_chunk_k(int tid, int nl, int n, int tw, int K)
     const bool last = ch.c0 + K >= n;
     ch.fend = last ? n + tw : ch.c0 + K;
     ch.bend = ch.c0 + K < n ? ch.c0 + K : n;
+    return ch;
+}
+
+// The same for a segment of n points that ends at a chunk's end of the whole
+// line's split, before the line's last point: the chunks are those of the whole
+// line, and one more chunk runs over the tw points behind the segment as the
+// whole line's next chunk does, from its own warm-up, so that the backward
+// warm-ups find the same bits as in the whole line.
+CH_HD Chunk seg_chunk(int tid, int nl, int n, int tw, int K)
+{
+    Chunk ch;
+    ch.l = tid % nl;
+    ch.c0 = tid / nl * K;
+    ch.live = ch.c0 <= n;
+    ch.fend = ch.c0 < n ? ch.c0 + K : n + tw;
+    ch.bend = ch.c0 < n ? ch.c0 + K : n;
     return ch;
 }
 
@@ -2333,21 +2351,27 @@ CH_HD void pass_line_program(X& ex, LineState<A>* st, const BoxDesc& bd, const P
             }
         }
     });
-    const int K = line_chunk_len(t.len, tw, YZ_CHAINS);
+    // a segment of a line split at its chunks' ends keeps the line's chunks
+    const int kline = bd.segk[pass - 1];
+    const int K = kline > 0 ? kline : line_chunk_len(t.len, tw, YZ_CHAINS);
+    const bool inner = kline > 0 && t.s0 + t.len < t.n;
+    auto chunk = [&](int tid) {
+        return inner ? seg_chunk(tid, Lw, t.len, tw, K) : line_chunk_k(tid, Lw, t.len, tw, K);
+    };
     ex.phase([&](int tid) {
-        const Chunk ch = line_chunk_k(tid, Lw, t.len, tw, K);
+        const Chunk ch = chunk(tid);
         line_f1<A>(ch, tile, Lw, tw, a1, a2, ic, st[ex.slot(tid)]);
     });
     ex.phase([&](int tid) {
-        const Chunk ch = line_chunk_k(tid, Lw, t.len, tw, K);
+        const Chunk ch = chunk(tid);
         line_f2<A>(ch, tile, Lw, tw, a1, a2, ic, st[ex.slot(tid)]);
     });
     ex.phase([&](int tid) {
-        const Chunk ch = line_chunk_k(tid, Lw, t.len, tw, K);
+        const Chunk ch = chunk(tid);
         line_b1<A>(ch, tile, Lw, tw, a1, a2, st[ex.slot(tid)]);
     });
     ex.phase([&](int tid) {
-        const Chunk ch = line_chunk_k(tid, Lw, t.len, tw, K);
+        const Chunk ch = chunk(tid);
         line_b2<A>(ch, tile, Lw, tw, a1, a2, st[ex.slot(tid)]);
     });
     // write the segment back (pass Z: C += dC); only the last batch of a

@@ -533,6 +533,38 @@ inline ch_status plan_dt(Plan& P, double dt)
     }
     seg = std::min(seg, lmax);
     P.seg_cap = seg;
+    // A single box of few lines splits them in the automatic plan, at the ends
+    // of the whole line's chunks, which leaves the bits as they are
+    // (seg_chunk).  A segment costs its rows and both warm-ups, and the fullest
+    // of the 256 CUs sets the time; only where that saves 48 rows: below, the
+    // passes' fixed time hides it (64^3, 96^3: no gain).  Per step, FP32 / FP64:
+    // 24 x 24 x 300 108 -> 75 / 112 -> 90 us, 31 x 300 x 30 107 -> 83 / 119 ->
+    // 107, 200 x 40 x 300 199 -> 174 / whole.
+    int segs[2] = {seg, seg}, segk[2] = {0, 0};
+    if (P.opt.seg_len == 0 && P.nbox == 1 && !P.e25) {
+        const chd::BoxDesc& d = P.boxes[0];
+        const int64_t nxb = (d.n[0] + P.lanes - 1) / P.lanes;
+        for (int p = 0; p < 2; ++p) {
+            const int n = d.n[1 + p];
+            const int K = chd::line_chunk_len(n, d.tw[0], chd::YZ_CHAINS);
+            bool one = n <= seg;   // whole lines, the same chunks in every substage
+            for (int k = 1; k < 3; ++k)
+                one = one && chd::line_chunk_len(n, d.tw[k], chd::YZ_CHAINS) == K;
+            if (!one) continue;
+            const int64_t lines = nxb * d.n[2 - p];
+            auto cost = [&](int len) {
+                return (lines * ((n + len - 1) / len) + 255) / 256 * (len + 2 * P.tw_max);
+            };
+            int best = n;
+            for (int m = chd::YZ_CHAINS - 1; m >= 1; --m)
+                if (m * K < n && cost(m * K) < cost(best)) best = m * K;
+            if (cost(n) - cost(best) >= 48) {
+                segs[p] = best;
+                segk[p] = K;
+            }
+        }
+        P.seg_cap = std::max(std::min(segs[0], d.n[1]), std::min(segs[1], d.n[2]));
+    }
     int64_t t0[3] = {0, 0, 0};
     P.seg_max[0] = P.seg_max[1] = 0;
     for (int b = 0; b < P.nbox; ++b) {
@@ -540,8 +572,10 @@ inline ch_status plan_dt(Plan& P, double dt)
         const int nx = d.n[0], ny = d.n[1], nz = d.n[2];
         if (P.xseg) d.x_rows = 1;
         d.zc = std::min(P.zc, nz);
-        d.seg[0] = std::min(seg, ny);
-        d.seg[1] = std::min(seg, nz);
+        d.seg[0] = std::min(segs[0], ny);
+        d.seg[1] = std::min(segs[1], nz);
+        d.segk[0] = segk[0];
+        d.segk[1] = segk[1];
         P.seg_max[0] = std::max(P.seg_max[0], d.seg[0]);
         P.seg_max[1] = std::max(P.seg_max[1], d.seg[1]);
         const int64_t nxb = (nx + P.lanes - 1) / P.lanes;
