@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 TARGET = os.path.join(HERE, "libch.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["ch_kernels.hip", "ch_lib.cpp"]
+SOURCES = ["ch_kernels.hip", "ch_fft.hip", "ch_lib.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed FP32 instructions stay off (see the design notes)

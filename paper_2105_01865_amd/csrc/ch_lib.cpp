@@ -1052,6 +1052,10 @@ struct ch_poisson {
     int nx = 0, ny = 0, nz = 0, zwalls = 0, prec = CH_FP64;
     double h = 0.0;
     hipStream_t stream = nullptr;
+    // own transforms along x, y (and z when periodic), or hipFFT's (own_transforms)
+    bool own = false;
+    chk::FftLine line[3] = {};
+    void* tw[3] = {nullptr, nullptr, nullptr};
     hipfftHandle fwd = 0, inv = 0;
     bool have_fwd = false, have_inv = false;
     void* phat = nullptr;   // 2 P^l - P^{l-1}
@@ -1098,6 +1102,40 @@ static ch_status scratch_ptr(double** out)
     g_scratch_ptr[dev] = (double*)p;
     *out = (double*)p;
     return CH_OK;
+}
+
+// The own transforms: x and y forward (and the solve along z, with its
+// transforms, when periodic); y and x back.
+template <typename T>
+static hipError_t poisson_forward(ch_poisson* p, const void* rhs)
+{
+    hipError_t err = chk::launch_fft_rows<T>(p->stream, p->line[0], rhs, p->spec, p->nxp,
+                                             (int64_t)p->ny * p->nz, false);
+    if (err == hipSuccess)
+        err = chk::launch_fft_cols<T>(p->stream, p->line[1], p->spec, p->nxp, p->nx / 2 + 1, p->nz,
+                                      false);
+    return err;
+}
+
+template <typename T>
+static hipError_t poisson_along_z(ch_poisson* p)
+{
+    if (p->own && !p->zwalls)
+        return chk::launch_fft_zsolve<T>(p->stream, p->line[2], p->spec, p->nx, p->ny, p->nxp, p->h,
+                                         p->sines);
+    return chk::launch_press_solve<T>(p->stream, p->zwalls, p->spec, p->cp, p->nx, p->ny, p->nz,
+                                      p->nxp, p->h, p->sines);
+}
+
+template <typename T>
+static hipError_t poisson_back(ch_poisson* p, void* P)
+{
+    hipError_t err = chk::launch_fft_cols<T>(p->stream, p->line[1], p->spec, p->nxp, p->nx / 2 + 1,
+                                             p->nz, true);
+    if (err == hipSuccess)
+        err = chk::launch_fft_rows<T>(p->stream, p->line[0], p->spec, P, p->nxp,
+                                      (int64_t)p->ny * p->nz, true);
+    return err;
 }
 
 extern "C" {
@@ -1566,11 +1604,30 @@ ch_status ch_batch_drops(ch_batch* b, int box, double threshold, int64_t cap, in
     return drops(b->e, box, threshold, cap, ndrops, root, cells);
 }
 
+// Where the own transforms take the place of hipFFT's (times of a solve, hipFFT's
+// first).  Periodic z: everywhere (512^3 FP32 2619 -> 1296 us, 300^3 FP64 1144 ->
+// 525, 240 x 180 x 160 FP64 205 -> 145, 32^3 FP32 35 -> 31) but for short rows
+// over many lines (32 x 128 x 128 FP64 46 -> 49 us, 30 x 128 x 100 FP32 36 -> 40:
+// threads and column tiles mostly masked).  Walls in FP64: large planes
+// (1024 x 1024 x 16 509 -> 402 us, 384 x 384 x 64 251 -> 193, 256^3 301 -> 293);
+// smaller ones are better off with hipFFT's fewer launches (128^3 71 -> 80,
+// 180 x 240 x 100 92 -> 105, 256 x 256 x 64 95 -> 98).  Walls in FP32 stay with
+// hipFFT (512^3: 1880 against 1290 us): after a step the mean mode of the next
+// right-hand side is what rounding left, which the solve along z amplifies by up
+// to nz^2, and other sums, no further from the truth, move a second step's P by
+// up to 4e-5 of it.
+static bool own_transforms(int nx, int ny, int nz, bool walls, int precision)
+{
+    const int64_t plane = (int64_t)nx * ny;
+    if (walls) return precision == CH_FP64 && plane >= 65536 && plane * nz >= 4194304;
+    return nx >= 36 || ny < 64;
+}
+
 static void poisson_free(ch_poisson* p)
 {
     if (p->have_fwd) (void)hipfftDestroy(p->fwd);
     if (p->have_inv) (void)hipfftDestroy(p->inv);
-    void* bufs[5] = {p->phat, p->rhs, p->spec, p->cp, p->sines};
+    void* bufs[8] = {p->phat, p->rhs, p->spec, p->cp, p->sines, p->tw[0], p->tw[1], p->tw[2]};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     delete p;
@@ -1602,6 +1659,10 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     const int padded = (p->nxp + 7) / 8 * 8;
     if (p->nxp >= 16 && (double)padded * p->ny * p->nz < 2147483647.0) p->nxp = padded;
     const size_t nm = (size_t)p->ny * p->nxp;
+    const int ext[3] = {p->nx, p->ny, p->nz};
+    p->own = own_transforms(p->nx, p->ny, p->nz, p->zwalls != 0, precision);
+    for (int d = 0; d < (p->zwalls ? 2 : 3); ++d)
+        p->own = chk::fft_radices(ext[d], precision == CH_FP32, &p->line[d]) && p->own;
     const hipfftType tf = precision == CH_FP64 ? HIPFFT_D2Z : HIPFFT_R2C;
     const hipfftType ti = precision == CH_FP64 ? HIPFFT_Z2D : HIPFFT_C2R;
     // z walls: 2-D transforms of the planes; periodic z: one 3-D transform
@@ -1609,13 +1670,16 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     const int first = p->zwalls ? 1 : 0, batch = p->zwalls ? p->nz : 1;
     const int rdist = p->nx * p->ny * (p->zwalls ? 1 : p->nz);
     const int cdist = p->nxp * p->ny * (p->zwalls ? 1 : p->nz);
-    const hipfftResult r1 = hipfftPlanMany(&p->fwd, 3 - first, dims + first, dims + first, 1, rdist,
-                                           cdims + first, 1, cdist, tf, batch);
-    p->have_fwd = r1 == HIPFFT_SUCCESS;
-    const hipfftResult r2 = hipfftPlanMany(&p->inv, 3 - first, dims + first, cdims + first, 1, cdist,
-                                           dims + first, 1, rdist, ti, batch);
-    p->have_inv = r2 == HIPFFT_SUCCESS;
-    if (!p->have_fwd || !p->have_inv) {
+    hipfftResult r1 = HIPFFT_SUCCESS, r2 = HIPFFT_SUCCESS;
+    if (!p->own) {
+        r1 = hipfftPlanMany(&p->fwd, 3 - first, dims + first, dims + first, 1, rdist,
+                            cdims + first, 1, cdist, tf, batch);
+        p->have_fwd = r1 == HIPFFT_SUCCESS;
+        r2 = hipfftPlanMany(&p->inv, 3 - first, dims + first, cdims + first, 1, cdist,
+                            dims + first, 1, rdist, ti, batch);
+        p->have_inv = r2 == HIPFFT_SUCCESS;
+    }
+    if (r1 != HIPFFT_SUCCESS || r2 != HIPFFT_SUCCESS) {
         poisson_free(p);
         return fail(CH_EHIP, "hipFFT plan creation failed (%d, %d)", (int)r1, (int)r2);
     }
@@ -1629,6 +1693,20 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
         poisson_free(p);
         return fail(CH_ENOMEM, "cannot allocate the pressure work arrays");
     }
+    if (p->own)
+        for (int d = 0; d < (p->zwalls ? 2 : 3); ++d) {
+            std::vector<double> w(2 * (size_t)ext[d]);
+            for (int m = 0; m < ext[d]; ++m) {
+                const double a = -2.0 * M_PI * m / ext[d];
+                w[2 * m] = std::cos(a);
+                w[2 * m + 1] = std::sin(a);
+            }
+            if (!upload_weights(&p->tw[d], w, precision)) {
+                poisson_free(p);
+                return fail(CH_ENOMEM, "cannot allocate the pressure work arrays");
+            }
+            p->line[d].tw = p->tw[d];
+        }
     if (!p->zwalls) {
         // ready on return: the handle's stream is set later
         hipError_t err = chk::launch_press_sines(nullptr, p->sines, p->nx, p->ny, p->nz);
@@ -1652,27 +1730,29 @@ ch_status ch_poisson_set_stream(ch_poisson* p, void* stream)
 
 static hipError_t poisson_enqueue(ch_poisson* p, const void* rhs, void* P)
 {
-    if (hipfftSetStream(p->fwd, p->stream) != HIPFFT_SUCCESS ||
-        hipfftSetStream(p->inv, p->stream) != HIPFFT_SUCCESS)
+    const bool dp = p->prec == CH_FP64;
+    if ((p->have_fwd && hipfftSetStream(p->fwd, p->stream) != HIPFFT_SUCCESS) ||
+        (p->have_inv && hipfftSetStream(p->inv, p->stream) != HIPFFT_SUCCESS))
         return hipErrorLaunchFailure;
-    hipfftResult r;
-    if (p->prec == CH_FP64)
+    hipError_t err = hipSuccess;
+    hipfftResult r = HIPFFT_SUCCESS;
+    if (p->own)
+        err = dp ? poisson_forward<double>(p, rhs) : poisson_forward<float>(p, rhs);
+    else if (dp)
         r = hipfftExecD2Z(p->fwd, (hipfftDoubleReal*)const_cast<void*>(rhs),
                           (hipfftDoubleComplex*)p->spec);
     else
         r = hipfftExecR2C(p->fwd, (hipfftReal*)const_cast<void*>(rhs), (hipfftComplex*)p->spec);
     if (r != HIPFFT_SUCCESS) return hipErrorLaunchFailure;
-    hipError_t err = p->prec == CH_FP64
-        ? chk::launch_press_solve<double>(p->stream, p->zwalls, p->spec, p->cp, p->nx, p->ny,
-                                          p->nz, p->nxp, p->h, p->sines)
-        : chk::launch_press_solve<float>(p->stream, p->zwalls, p->spec, p->cp, p->nx, p->ny,
-                                         p->nz, p->nxp, p->h, p->sines);
+    if (err == hipSuccess) err = dp ? poisson_along_z<double>(p) : poisson_along_z<float>(p);
     if (err != hipSuccess) return err;
-    if (p->prec == CH_FP64)
+    if (p->own)
+        err = dp ? poisson_back<double>(p, P) : poisson_back<float>(p, P);
+    else if (dp)
         r = hipfftExecZ2D(p->inv, (hipfftDoubleComplex*)p->spec, (hipfftDoubleReal*)P);
     else
         r = hipfftExecC2R(p->inv, (hipfftComplex*)p->spec, (hipfftReal*)P);
-    return r == HIPFFT_SUCCESS ? hipSuccess : hipErrorLaunchFailure;
+    return r == HIPFFT_SUCCESS ? err : hipErrorLaunchFailure;
 }
 
 ch_status ch_poisson_solve(ch_poisson* p, const void* rhs, void* P)
