@@ -1107,24 +1107,43 @@ k_press_prep(const T* __restrict__ P, T* __restrict__ Pold, T* __restrict__ phat
     }
 }
 
-// The cell kernels of the pressure step take tiles of TX x-columns by TY
-// rows and march each column up TZ planes, carrying the plane below in
+// The cell kernels of the pressure step take tiles of tx (2^lx) x-columns by ty
+// rows and march each column up tz planes, carrying the plane below in
 // registers, so no plane is fetched twice for its z neighbours.  Planes are
 // addressed through 32-bit byte offsets from a per-plane base (a plane is
-// under 4 GiB).
+// under 4 GiB).  Work-groups of rhs_threads and UPD_THREADS.
 struct PressTile {
-    int tx, ty, tz;
+    int lx, tx, ty, tz;
 };
-constexpr PressTile RHS_TILE = {256, 2, 8}, UPD_TILE = {256, 1, 2};
-constexpr PressTile RHS_TILE64 = {64, 4, 16}, UPD_TILE64 = {256, 1, 2};
 template <typename T>
-constexpr PressTile rhs_tile() { return sizeof(T) == 8 ? RHS_TILE64 : RHS_TILE; }
-template <typename T>
-constexpr PressTile upd_tile() { return sizeof(T) == 8 ? UPD_TILE64 : UPD_TILE; }
+constexpr int rhs_threads() { return sizeof(T) == 8 ? 256 : 512; }
+constexpr int UPD_THREADS = 256;
 
 __host__ __device__ __forceinline__ int64_t press_tiles(PressTile p, int nx, int ny, int nz)
 {
     return (int64_t)((nx + p.tx - 1) / p.tx) * ((ny + p.ty - 1) / p.ty) * ((nz + p.tz - 1) / p.tz);
+}
+
+// Tile of a work-group of `threads`: of the widths `widest` down to 64 (FP64) or
+// 128 columns (FP32: 512 bytes a row; 256 bytes cost more in lines fetched twice
+// than they save in padding, 180 x 240 x 100: the step 195 us against 184) the
+// one that pads a row of nx least, the widest of equals, and marches of up to
+// `longest` planes, halved down to `shortest` while there are under 2048 tiles
+// (eight groups per CU).  Against 256 columns and the longest march everywhere (us
+// per pressure step): 300^3 FP32 1057 -> 909, FP64 1669 -> 1477, 320 x 200 x 150
+// FP32 357 -> 326, 64^3 FP64 92 -> 76, 90 x 300 x 40 FP64 148 -> 131; 512^3 FP32,
+// where nothing changes, 3922 / 3913.
+template <typename T>
+inline PressTile press_tile(int threads, int widest, int longest, int shortest, int nx, int ny,
+                            int nz)
+{
+    PressTile p{0, widest, threads / widest, longest};
+    for (int w = widest; w >= (sizeof(T) == 8 ? 64 : 128); w /= 2)
+        if ((nx + w - 1) / w * w < (nx + p.tx - 1) / p.tx * p.tx) p.tx = w;
+    p.ty = threads / p.tx;
+    while ((1 << p.lx) < p.tx) ++p.lx;
+    while (p.tz / 2 >= shortest && press_tiles(p, nx, ny, nz) < 2048) p.tz /= 2;
+    return p;
 }
 
 // Column of thread t in task `task`: x, y and the march z0 .. z1 - 1; false
@@ -1136,8 +1155,8 @@ __device__ __forceinline__ bool press_column(PressTile p, int64_t task, int t, i
     const int bx = (int)(task % tx);
     const int64_t rest = task / tx;
     const int by = (int)(rest % ty), bz = (int)(rest / ty);
-    *x = bx * p.tx + t % p.tx;
-    *y = by * p.ty + t / p.tx;
+    *x = bx * p.tx + (t & (p.tx - 1));
+    *y = by * p.ty + (t >> p.lx);
     *z0 = bz * p.tz;
     *z1 = *z0 + p.tz < nz ? *z0 + p.tz : nz;
     return *x < nx && *y < ny;
@@ -1146,8 +1165,8 @@ __device__ __forceinline__ bool press_column(PressTile p, int64_t task, int t, i
 // Right-hand side of eq-newpoi at every cell:
 // div[(1 - rho2/rho_f) grad Phat] + (rho2/dt) div u*.
 template <typename T>
-__global__ void __launch_bounds__(rhs_tile<T>().tx * rhs_tile<T>().ty)
-k_press_rhs(PressArgs a, const T* __restrict__ C, const T* __restrict__ ph,
+__global__ void __launch_bounds__(rhs_threads<T>())
+k_press_rhs(PressTile tile, PressArgs a, const T* __restrict__ C, const T* __restrict__ ph,
             const T* __restrict__ u, const T* __restrict__ v, const T* __restrict__ w,
             T* __restrict__ rhs)
 {
@@ -1157,10 +1176,10 @@ k_press_rhs(PressArgs a, const T* __restrict__ C, const T* __restrict__ ph,
     const uint32_t pbytes = (uint32_t)(plane * sT);
     const T ih = T(1.0 / a.h), r2 = T(a.rho2), sdiv = T(a.rho2 / a.dt);
     auto at = [&](const T* f, int z) { return chd::PlaneRef<T>(f + (int64_t)z * plane, pbytes); };
-    const int64_t ntask = press_tiles(rhs_tile<T>(), nx, ny, nz);
+    const int64_t ntask = press_tiles(tile, nx, ny, nz);
     for (int64_t task = blockIdx.x; task < ntask; task += gridDim.x) {
         int x, y, z0, z1;
-        if (!press_column(rhs_tile<T>(), task, (int)threadIdx.x, nx, ny, nz, &x, &y, &z0, &z1)) continue;
+        if (!press_column(tile, task, (int)threadIdx.x, nx, ny, nz, &x, &y, &z0, &z1)) continue;
         const int xm = x > 0 ? x - 1 : nx - 1, xp = x + 1 < nx ? x + 1 : 0;
         const int ym = y > 0 ? y - 1 : ny - 1, yp = y + 1 < ny ? y + 1 : 0;
         const uint32_t oc = (uint32_t)(y * nx + x) * sT, oxm = (uint32_t)(y * nx + xm) * sT,
@@ -1496,8 +1515,8 @@ k_press_div(T* __restrict__ spec, int nx, int ny, int nz, int nxp, double h, dou
 // eq-u on the low faces of every cell (the wall faces of z stay as they are),
 // z-marching tiles as for the right-hand side.
 template <typename T>
-__global__ void __launch_bounds__(upd_tile<T>().tx * upd_tile<T>().ty)
-k_press_update(PressArgs a, const T* __restrict__ C, const T* __restrict__ P,
+__global__ void __launch_bounds__(UPD_THREADS)
+k_press_update(PressTile tile, PressArgs a, const T* __restrict__ C, const T* __restrict__ P,
                const T* __restrict__ ph, T* __restrict__ u, T* __restrict__ v, T* __restrict__ w)
 {
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -1506,10 +1525,10 @@ k_press_update(PressArgs a, const T* __restrict__ C, const T* __restrict__ P,
     const uint32_t pbytes = (uint32_t)(plane * sT);
     const T ih = T(1.0 / a.h), ir2 = T(1.0 / a.rho2), dt = T(a.dt);
     auto at = [&](const T* f, int z) { return chd::PlaneRef<T>(f + (int64_t)z * plane, pbytes); };
-    const int64_t ntask = press_tiles(upd_tile<T>(), nx, ny, nz);
+    const int64_t ntask = press_tiles(tile, nx, ny, nz);
     for (int64_t task = blockIdx.x; task < ntask; task += gridDim.x) {
         int x, y, z0, z1;
-        if (!press_column(upd_tile<T>(), task, (int)threadIdx.x, nx, ny, nz, &x, &y, &z0, &z1)) continue;
+        if (!press_column(tile, task, (int)threadIdx.x, nx, ny, nz, &x, &y, &z0, &z1)) continue;
         const int xm = x > 0 ? x - 1 : nx - 1, ym = y > 0 ? y - 1 : ny - 1;
         const uint32_t oc = (uint32_t)(y * nx + x) * sT, oxm = (uint32_t)(y * nx + xm) * sT,
                        oym = (uint32_t)(ym * nx + x) * sT;
@@ -1840,11 +1859,12 @@ template <typename T>
 hipError_t launch_press_rhs(hipStream_t st, const PressArgs& a, const void* C, const void* phat,
                             const void* u, const void* v, const void* w, void* rhs)
 {
-    constexpr PressTile tl = rhs_tile<T>();
+    const PressTile tl = press_tile<T>(rhs_threads<T>(), sizeof(T) == 8 ? 64 : 256,
+                                    sizeof(T) == 8 ? 16 : 8, 4, a.nx, a.ny, a.nz);
     const int64_t tiles = press_tiles(tl, a.nx, a.ny, a.nz);
     hipLaunchKernelGGL((k_press_rhs<T>), dim3((unsigned)(tiles < 1048576 ? tiles : 1048576)),
-                       dim3(tl.tx * tl.ty), 0, st, a, (const T*)C, (const T*)phat, (const T*)u,
-                       (const T*)v, (const T*)w, (T*)rhs);
+                       dim3(rhs_threads<T>()), 0, st, tl, a, (const T*)C, (const T*)phat,
+                       (const T*)u, (const T*)v, (const T*)w, (T*)rhs);
     return hipGetLastError();
 }
 
@@ -1883,10 +1903,10 @@ template <typename T>
 hipError_t launch_press_update(hipStream_t st, const PressArgs& a, const void* C, const void* P,
                                const void* phat, void* u, void* v, void* w)
 {
-    constexpr PressTile tl = upd_tile<T>();
+    const PressTile tl = press_tile<T>(UPD_THREADS, 256, 2, 2, a.nx, a.ny, a.nz);
     const int64_t tiles = press_tiles(tl, a.nx, a.ny, a.nz);
     hipLaunchKernelGGL((k_press_update<T>), dim3((unsigned)(tiles < 1048576 ? tiles : 1048576)),
-                       dim3(tl.tx * tl.ty), 0, st, a, (const T*)C, (const T*)P, (const T*)phat,
+                       dim3(UPD_THREADS), 0, st, tl, a, (const T*)C, (const T*)P, (const T*)phat,
                        (T*)u, (T*)v, (T*)w);
     return hipGetLastError();
 }
