@@ -2277,7 +2277,10 @@ struct Vec16 {
     typedef T type __attribute__((vector_size(16)));
 };
 
-template <typename T, typename A, class X>
+// SPLIT: whether lines split at their chunks' ends can occur (0: no, 1: yes).  A
+// kernel of its own for them: the chunk's selection costs every launch of a small
+// box 0.15 us (32^3 FP64: ten steps 756 -> 744 us).
+template <typename T, typename A, class X, int SPLIT = 1>
 CH_HD void pass_line_program(X& ex, LineState<A>* st, const BoxDesc& bd, const PassArgs& pa,
                              int pass, int task, const T* __restrict__ Qin,
                              T* __restrict__ Qout, unsigned char* smem)
@@ -2352,7 +2355,7 @@ CH_HD void pass_line_program(X& ex, LineState<A>* st, const BoxDesc& bd, const P
         }
     });
     // a segment of a line split at its chunks' ends keeps the line's chunks
-    const int kline = bd.segk[pass - 1];
+    const int kline = SPLIT ? bd.segk[pass - 1] : 0;
     const int K = kline > 0 ? kline : line_chunk_len(t.len, tw, YZ_CHAINS);
     const bool inner = kline > 0 && t.s0 + t.len < t.n;
     auto chunk = [&](int tid) {

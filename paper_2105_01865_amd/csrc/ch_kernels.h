@@ -31,10 +31,11 @@ hipError_t launch_pass_x_e25(int nwg, int nth, size_t lds, hipStream_t st,
                              const chd::BoxDesc* boxes, const chd::PassArgs& pa, const void* C,
                              const void* U, const void* V, const void* W, void* E, void* Q);
 
+// split: the box's lines are split at their chunks' ends (BoxDesc::segk).
 template <typename T, typename A>
 hipError_t launch_pass_line(int pass, int nwg, int nthreads, size_t lds, hipStream_t st,
                             const chd::BoxDesc* boxes, int nbox, const chd::PassArgs& pa,
-                            const void* Qin, void* Qout);
+                            const void* Qin, void* Qout, bool split);
 
 template <typename T>
 hipError_t launch_mass(int nblk, int nbox, hipStream_t st, const chd::BoxDesc* boxes,

@@ -114,7 +114,7 @@ k_pass_x_e25(const chd::BoxDesc* __restrict__ boxes, chd::PassArgs pa, const T* 
                                                  smem);
 }
 
-template <typename T, typename A, int PASS>
+template <typename T, typename A, int PASS, int SPLIT>
 __global__ void __launch_bounds__(512)
 k_pass_line(const chd::BoxDesc* __restrict__ boxes, int nbox, chd::PassArgs pa,
             const T* __restrict__ Qin, T* __restrict__ Qout)
@@ -124,7 +124,8 @@ k_pass_line(const chd::BoxDesc* __restrict__ boxes, int nbox, chd::PassArgs pa,
     const int b = chd::find_box(boxes, nbox, PASS, task);
     chd::GpuExec ex{(int)threadIdx.x, (int)blockDim.x};
     chd::LineState<A> st;
-    chd::pass_line_program<T, A>(ex, &st, boxes[b], pa, PASS, task, Qin, Qout, smem);
+    chd::pass_line_program<T, A, chd::GpuExec, SPLIT>(ex, &st, boxes[b], pa, PASS, task, Qin, Qout,
+                                                      smem);
 }
 
 // Mass, stage 1 body: block `blk` of box bd (MASS_BLOCK elements of C),
@@ -1684,21 +1685,18 @@ hipError_t launch_pass_x_e25(int nwg, int nth, size_t lds, hipStream_t st,
 template <typename T, typename A>
 hipError_t launch_pass_line(int pass, int nwg, int nthreads, size_t lds, hipStream_t st,
                             const chd::BoxDesc* boxes, int nbox, const chd::PassArgs& pa,
-                            const void* Qin, void* Qout)
+                            const void* Qin, void* Qout, bool split)
 {
-    const void* fn = pass == chd::PASS_Y ? (const void*)&k_pass_line<T, A, chd::PASS_Y>
-                                         : (const void*)&k_pass_line<T, A, chd::PASS_Z>;
+    const auto fn = pass == chd::PASS_Y
+        ? (split ? k_pass_line<T, A, chd::PASS_Y, 1> : k_pass_line<T, A, chd::PASS_Y, 0>)
+        : (split ? k_pass_line<T, A, chd::PASS_Z, 1> : k_pass_line<T, A, chd::PASS_Z, 0>);
     if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)lds);
+        hipError_t e = hipFuncSetAttribute((const void*)fn,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    if (pass == chd::PASS_Y)
-        hipLaunchKernelGGL((k_pass_line<T, A, chd::PASS_Y>), dim3(nwg), dim3(nthreads), lds, st,
-                           boxes, nbox, pa, (const T*)Qin, (T*)Qout);
-    else
-        hipLaunchKernelGGL((k_pass_line<T, A, chd::PASS_Z>), dim3(nwg), dim3(nthreads), lds, st,
-                           boxes, nbox, pa, (const T*)Qin, (T*)Qout);
+    hipLaunchKernelGGL(fn, dim3(nwg), dim3(nthreads), lds, st, boxes, nbox, pa, (const T*)Qin,
+                       (T*)Qout);
     return hipGetLastError();
 }
 
@@ -1923,7 +1921,7 @@ hipError_t launch_press_update(hipStream_t st, const PressArgs& a, const void* C
                                                 const void*, const void*, void*, void*);        \
     template hipError_t launch_pass_line<T, A>(int, int, int, size_t, hipStream_t,              \
                                                const chd::BoxDesc*, int, const chd::PassArgs&,  \
-                                               const void*, void*);
+                                               const void*, void*, bool);
 
 CH_INSTANTIATE(double, double)
 CH_INSTANTIATE(float, float)

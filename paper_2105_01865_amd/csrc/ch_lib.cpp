@@ -249,11 +249,11 @@ hipError_t enqueue_substage(Engine& e, int k, const void* u, const void* v, cons
         else if (p == 1)
             err = chk::launch_pass_line<T, A>(chd::PASS_Y, e.P.ntask[1], e.P.yz_threads,
                                               e.P.lds[1], e.stream, e.d_boxes, e.P.nbox, pa, e.qa,
-                                              e.qb);
+                                              e.qb, e.P.boxes[0].segk[0] > 0);
         else
             err = chk::launch_pass_line<T, A>(chd::PASS_Z, e.P.ntask[2], e.P.yz_threads,
                                               e.P.lds[2], e.stream, e.d_boxes, e.P.nbox, pa, e.qb,
-                                              e.C);
+                                              e.C, e.P.boxes[0].segk[1] > 0);
         if (e.prof && a && b) {
             (void)hipEventRecord(b, e.stream);
             e.ev_pending.push_back({p, {a, b}});
