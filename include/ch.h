@@ -283,8 +283,8 @@ ch_status ch_step_multires(ch_state* s, ch_interp* ip, const void* uc, const voi
  * y; z periodic (z_walls = 0: w has nz planes) or between two walls
  * (z_walls = 1: w has nz + 1 planes, zero on both walls, dP/dz = 0 there).
  * The density is rho = rho2 + (rho1 - rho2) clamp(C, 0, 1) (rho2 <= rho1),
- * taken on a face as the mean of its two cells.  Creation makes the hipFFT
- * plans and the work arrays (three fields and a spectrum); nx, ny, nz >= 2
+ * taken on a face as the mean of its two cells.  Creation makes the transforms'
+ * tables or plans and the work arrays (three fields and a spectrum); nx, ny, nz >= 2
  * (CH_EINVAL), fewer than 2^31 cells and planes (nx ny) under 4 GiB
  * (CH_EUNSUPPORTED).  Device memory in
  * the given precision; work is enqueued on the handle's stream.
