@@ -323,12 +323,14 @@ void ch_poisson_destroy(ch_poisson* p);
  * ch_step (tune again).  out receives the chosen plan, its ms per step, the
  * automatic plan's ms per step and the number of candidates timed (the
  * automatic plan is also run once first, untimed for the choice, to warm the
- * device up). */
+ * device up).  x_rows, z_chunk and seg_len of the chosen plan, given as the
+ * options of another state of the box, give the same bits there. */
 typedef struct {
     int x_rows, z_chunk;
     double ms_per_step, auto_ms_per_step;
     int candidates;
-    int seg_len;   /* segment length of the y and z line passes */
+    int seg_len;   /* segment length of the y and z line passes; 0: the
+                      automatic plan, which splits a small box's lines */
 } ch_tune;
 ch_status ch_autotune(ch_state* s, const void* u, const void* v, const void* w, double dt,
                       int steps, ch_tune* out);
@@ -367,7 +369,8 @@ ch_status ch_batch_profile_read(ch_batch* b, int kernel, double* total_ms, int64
 
 /* Launch configuration the library chose (or was given) for the state at
  * its last time step: cfg[0] = x rows per x-pass work-group, cfg[1] = y/z
- * line segment, cfg[2] = threads per y/z work-group, cfg[3..5] = warm-up
+ * line segment (0 where the automatic plan splits a small box's lines, each
+ * pass in its own way), cfg[2] = threads per y/z work-group, cfg[3..5] = warm-up
  * length of the line recurrences in substages 1..3 (first box), cfg[6] = 1
  * if the solves run in double, cfg[7] = planes an x-pass work-group marches
  * over. */

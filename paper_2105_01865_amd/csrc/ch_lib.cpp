@@ -902,7 +902,7 @@ ch_status autotune(Engine& e, const void* u, const void* v, const void* w, doubl
     if (err != hipSuccess) return fail(CH_EHIP, "cannot restore C: %s", hipGetErrorString(err));
     out->x_rows = e.P.x_rows;
     out->z_chunk = e.P.zc;
-    out->seg_len = e.P.seg_cap;
+    out->seg_len = chp::seg_option(e.P);
     out->ms_per_step = best_ms;
     out->auto_ms_per_step = auto_ms;
     out->candidates = tried;
@@ -1279,7 +1279,7 @@ ch_status ch_get_config(const ch_state* s, int cfg[8])
     if (!cfg) return fail(CH_EINVAL, "null output");
     const chp::Plan& P = s->e.P;
     cfg[0] = P.x_rows;
-    cfg[1] = P.seg_cap;
+    cfg[1] = chp::seg_option(P);
     cfg[2] = P.yz_threads;
     for (int k = 0; k < 3; ++k) cfg[3 + k] = P.boxes[0].tw[k];
     cfg[6] = P.acc64 ? 1 : 0;

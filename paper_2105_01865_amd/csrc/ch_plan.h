@@ -139,6 +139,15 @@ struct Plan {
 
 inline size_t esize(int prec) { return prec == CH_FP64 ? 8 : 4; }
 
+// The seg_len option that gives the plan again: its segment length, or 0
+// (automatic) where the automatic plan splits lines at their chunks' ends,
+// which no one length stands for (an explicit length splits both passes, and
+// each of its segments has chunks of its own and so other bits).
+inline int seg_option(const Plan& P)
+{
+    return P.boxes[0].segk[0] > 0 || P.boxes[0].segk[1] > 0 ? 0 : P.seg_cap;
+}
+
 inline void default_opts(ch_opts* o)
 {
     *o = ch_opts{};
