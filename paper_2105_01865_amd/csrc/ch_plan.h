@@ -490,34 +490,44 @@ inline ch_status plan_dt(Plan& P, double dt)
         // that allows (each task reloads 6 planes to start its march)
         const int64_t rows_total = cells / std::max(1, nxm);
         zc = (int)std::max<int64_t>(1, std::min<int64_t>(16, rows_total / R / 2048));
-        if (row_ok && zc <= 12) {
-            // the row program marches up to 12 planes to come down to the
-            // threads of 1024 groups of 256: 2048 groups prime and solve too
-            // often (per step, 96^3 FP64 142 -> 129 us, 80^3 120 -> 110, 300 x
-            // 100 x 50 FP32 169 -> 144, 128^3 135 -> 130); of the five counts
-            // down from there, a single box takes the one whose fullest CU has
-            // least to do, a task costing its planes and 2.5 more (152 x 235 x
-            // 89 FP64: 12 planes 322 us, 10 planes 313)
+        int zfit = 0;
+        // the row program marches up to 12 planes to come down to the threads of
+        // 1024 groups of 256: 2048 groups prime and solve too often (per step,
+        // 96^3 FP64 142 -> 129 us, 80^3 120 -> 110, 300 x 100 x 50 FP32 169 ->
+        // 144, 128^3 135 -> 130); of the five counts down from there it takes the
+        // one whose fullest CU has least to do, a task costing its planes and 2.5
+        // more (152 x 235 x 89 FP64: 12 planes 322 us, 10 planes 313).  Groups of
+        // one wave already march further by the 2048 (64^3 FP64 with one row per
+        // task 88 us, 94 at half the march).  A batch does so where its x pass is
+        // one launch and the 2048 give it at most 5 planes (two boxes of 160 x 80
+        // x 40 FP64 172 -> 159 us, four of 65 x 119 x 29 201 -> 185); beyond, it
+        // gains nothing (two of 176 x 97 x 65 231 -> 235), and launches of one row
+        // mode each are short of groups (75 x 184 x 44 and 176 x 37 x 101 238 ->
+        // 253).
+        const bool one_launch = std::count(bmode.begin(), bmode.end(), bmode[0]) == P.nbox;
+        if (row_ok && zc <= (P.nbox == 1 ? 12 : 5) && one_launch) {
             const int64_t target = 1024 * 256 / std::max(64, P.x_threads);
             const int zn = (int)std::max<int64_t>(1, std::min<int64_t>(12, (rows_total / R + target / 2) / target));
-            // (groups of one wave already march further by the 2048: 64^3 FP64
-            // with one row per task 88 us, 94 at half the march)
-            if (zn >= zc) {
-                zc = zn;
-                if (P.nbox == 1) {
-                    const int64_t nyb = (P.boxes[0].n[1] + R - 1) / R, nz = P.boxes[0].n[2];
-                    double best = INFINITY;
-                    for (int z = zn; z >= std::max(1, zn - 4); --z) {
-                        const int64_t tasks = nyb * ((nz + z - 1) / z);
-                        const double cost = (double)((tasks + 255) / 256) * (z + 2.5);
-                        if (cost < best) {
-                            best = cost;
-                            zc = z;
-                        }
-                    }
+            double best = INFINITY;
+            for (int z = zn; zn >= zc && z >= std::max(1, zn - 4); --z) {
+                int64_t tasks = 0;
+                double work = 0.0;
+                for (int b = 0; b < P.nbox; ++b) {
+                    const int64_t ny = P.boxes[b].n[1], nz = P.boxes[b].n[2];
+                    const int64_t zb = std::min<int64_t>(z, nz);
+                    const int r = P.nbox == 1 ? R : rows_of(b);
+                    const int64_t t = (ny + r - 1) / r * ((nz + zb - 1) / zb);
+                    tasks += t;
+                    work += (double)t * (zb + 2.5);
+                }
+                const double cost = (double)((tasks + 255) / 256) * work / tasks;
+                if (cost < best) {
+                    best = cost;
+                    zfit = z;
                 }
             }
         }
+        if (zfit > 0) zc = zfit;
         zc = std::min(zc, zlim);
         while (zc > 1 && !lds_fits(zc, false)) --zc;
     }
