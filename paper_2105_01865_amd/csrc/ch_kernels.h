@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "ch_device.h"
+#include "ch_route.h"
 
 namespace chk {
 
@@ -59,11 +60,6 @@ hipError_t launch_check_velocity(hipStream_t st, const chd::BoxDesc* boxes, int 
 // of every 4 consecutive targets 4t .. 4t+3 lie within the 6 cyclically
 // consecutive coarse points starting at target 4t's first tap.  Weights of
 // the y and z stencils are in the working precision.
-constexpr int MARCH_BAND = 8;   // target rows of a sub-band of the marching kernel
-// Where the taps of consecutive targets start, within groups of 4 in x and
-// MARCH_BAND in y: anywhere, at 0 0 1 1 .., or at 0 1 1 2 ..
-enum { MARCH_ANY = 0, MARCH_FACE = 1, MARCH_CENTRE = 2 };
-
 struct InterpArgs {
     const void* src;        // coarse component [.][sy][sx]
     void* dst;              // target [tnz][tny][tnx]
@@ -155,44 +151,6 @@ template <typename T>
 hipError_t launch_press_solve(hipStream_t st, int zwalls, void* spec, void* cp, int nx, int ny,
                               int nz, int nxp, double h, const double* sines);
 hipError_t launch_press_sines(hipStream_t st, double* out, int nx, int ny, int nz);
-// Lines of the library's own transforms (ch_fft.hip): n points, a product of 2,
-// 3 and 5 up to FFT_MAX, their passes' radices, and the twiddles
-// exp(-2 pi i m / n), m < n, in the working precision (device memory).
-constexpr int FFT_MAX = 1024;
-struct FftLine {
-    int n, passes, p2;   // p2: n is a power of two
-    int radix[10];
-    const void* tw;
-};
-// Radices of n's passes, as few as possible and then of the least sum (six:
-// also 6, which FP32 has the registers for); false where the transforms do not
-// take n.
-inline bool fft_radices(int n, bool six, FftLine* f)
-{
-    f->n = n;
-    f->passes = 0;
-    f->p2 = (n & (n - 1)) == 0;
-    f->tw = nullptr;
-    if (n < 2 || n > FFT_MAX) return false;
-    FftLine best = *f;
-    int least = 0;
-    auto search = [&](auto&& self, const FftLine& l, int rest, int top, int cost) -> void {
-        if (rest == 1 && (least == 0 || cost < least)) {
-            best = l;
-            least = cost;
-        }
-        if (rest == 1 || l.passes == 10) return;
-        for (int r : {8, 6, 5, 4, 3, 2}) {
-            if (r > top || rest % r != 0 || (r == 6 && !six)) continue;
-            FftLine m = l;
-            m.radix[m.passes++] = r;
-            self(self, m, rest / r, r, cost + 100 + r);
-        }
-    };
-    search(search, *f, n, 8, 0);
-    *f = best;
-    return least > 0;
-}
 // Columns along the middle axis of spec [nplane][n][pitch] complex, in place,
 // columns 0 .. ncol - 1, unscaled.
 template <typename T>

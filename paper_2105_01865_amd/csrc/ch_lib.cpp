@@ -24,6 +24,7 @@
 #include "ch_device.h"
 #include "ch_kernels.h"
 #include "ch_plan.h"
+#include "ch_route.h"
 
 namespace {
 
@@ -489,72 +490,6 @@ bool interp_bands(const std::vector<int>& iy, int64_t tny, int sx, int sy, size_
     return false;
 }
 
-// Whether the x taps of every 4 consecutive targets 4t .. 4t+3 lie within
-// the 6 cyclically consecutive source points from target 4t's first tap.
-bool interp_xwin(const std::vector<int>& ix, int64_t tnx, int sx)
-{
-    for (int64_t i0 = 0; i0 < tnx; i0 += 4) {
-        const int ws = ix[4 * i0];
-        for (int64_t i = i0; i < std::min<int64_t>(tnx, i0 + 4); ++i)
-            for (int q = 0; q < 4; ++q)
-                if ((ix[4 * i + q] - ws + sx) % sx >= 6) return false;
-    }
-    return true;
-}
-
-// Most work-groups of a marching transfer (beyond, its groups march further):
-// whole rounds of those resident (6 per CU in single precision, 3 in double),
-// two and eight.  512^3, us per component: FP32 1024 groups 199, 2048 181, 3008
-// 169, 3328 182, 8192 184; FP64 2048 423, 4096 345, 6144 331, 8192 328.
-template <typename T>
-constexpr int64_t march_wg()
-{
-    return sizeof(T) == 4 ? 3072 : 6144;
-}
-// Single-precision targets from this size on are stored non-temporally: they
-// are out of the caches before anything reads them (512^3 181 against 187 us).
-// Below, the step or the integration that follows reads them from the caches,
-// and in double precision a lane's 32 bytes are two half-line stores that only
-// a cache joins (256^3 FP64 54 against 63 us, with the integration 112 against
-// 140).
-constexpr int64_t MARCH_NT_BYTES = 256ll << 20;
-
-// Coarse rows a thread of the marching transfer holds (8 or 11), or 0 where it
-// does not apply: coarse rows of at most 256 points, at most 1024 targets in x
-// whose taps lie in 6-point windows, and in every 8 target rows from a multiple
-// of 8 on consecutive y taps that start at most one coarse row later per row.
-int interp_march_rows(const std::vector<int>& iy, int64_t tnx, int64_t tny, int sx, int sy, int xwin)
-{
-    if (sx > 256 || tnx > 1024 || !xwin || sy < 4) return 0;
-    int span = 0;
-    for (int64_t j = 0; j < tny; ++j) {
-        const int64_t jb = j / chk::MARCH_BAND * chk::MARCH_BAND;
-        for (int q = 1; q < 4; ++q)
-            if (iy[4 * j + q] != (iy[4 * j] + q) % sy) return 0;
-        const int l = (iy[4 * j] - iy[4 * jb] + sy) % sy;
-        const int prev = j == jb ? 0 : (iy[4 * (j - 1)] - iy[4 * jb] + sy) % sy;
-        if (l < prev || l > prev + 1) return 0;
-        span = std::max(span, l + 4);
-    }
-    return span <= 8 ? 8 : span <= 11 ? 11 : 0;
-}
-
-// The pattern (chk::MARCH_*) of the targets' first taps in groups of `group`,
-// each target's taps consecutive.
-int interp_pattern(const std::vector<int>& ix, int64_t tn, int n, int group)
-{
-    bool face = true, centre = true;
-    for (int64_t i = 0; i < tn; ++i) {
-        for (int q = 1; q < 4; ++q)
-            if (ix[4 * i + q] != (ix[4 * i] + q) % n) return chk::MARCH_ANY;
-        const int g = (int)(i % group);
-        const int d = (ix[4 * i] - ix[4 * (i - g)] + n) % n;
-        face = face && d == g / 2;
-        centre = centre && d == (g + 1) / 2;
-    }
-    return face ? chk::MARCH_FACE : centre ? chk::MARCH_CENTRE : chk::MARCH_ANY;
-}
-
 template <typename T>
 hipError_t launch_transfer(const Transfer& t, hipStream_t st, const void* src, void* dst)
 {
@@ -585,16 +520,13 @@ hipError_t launch_transfer(const Transfer& t, hipStream_t st, const void* src, v
     ia.yp = t.yp;
     ia.iy0 = t.iy0;
     if (t.rm) {
-        // a wave's columns belong to one sub-band; planes per group so that the
-        // chip has a few groups per CU, at least 4 to reuse the stencils
-        ia.sxw = (ia.sx + 63) / 64 * 64;
-        ia.nsub = std::max(1, 256 / ia.sxw);
-        const int rows = chk::MARCH_BAND * ia.nsub;
-        ia.nband = (ia.tny + rows - 1) / rows;
-        ia.kc = std::max(4, (int)(((int64_t)ia.tnz * ia.nband + march_wg<T>() - 1) / march_wg<T>()));
-        ia.kc = std::min(ia.kc, ia.tnz);
-        ia.nchunk = (ia.tnz + ia.kc - 1) / ia.kc;
-        ia.nt = sizeof(T) == 4 && t.tn[0] * t.tn[1] * t.tn[2] * (int64_t)sizeof(T) >= MARCH_NT_BYTES;
+        const chp::MarchShape m = chp::march_shape(sizeof(T), t.sx, t.tn);
+        ia.sxw = m.sxw;
+        ia.nsub = m.nsub;
+        ia.nband = m.nband;
+        ia.kc = m.kc;
+        ia.nchunk = m.nchunk;
+        ia.nt = m.nt;
     }
     return chk::launch_interp<T>(st, ia);
 }
@@ -1014,10 +946,14 @@ ch_status build_transfer(Transfer& t, const chp::SrcAxis* const src[3],
         const int base = band[2 * ((q / 4) / t.jb)];
         ly[q] = (int)(((idx[1][q] - base + sy) % sy) * sx);
     }
-    t.xwin = interp_xwin(idx[0], t.tn[0], (int)sx) ? 1 : 0;
-    t.rm = interp_march_rows(idx[1], t.tn[0], t.tn[1], (int)sx, (int)sy, t.xwin);
-    t.xp = interp_pattern(idx[0], t.tn[0], (int)sx, 4);
-    t.yp = interp_pattern(idx[1], t.tn[1], (int)sy, chk::MARCH_BAND);
+    t.xwin = chp::interp_xwin(idx[0], t.tn[0], (int)sx) ? 1 : 0;
+    t.rm = chp::interp_march_rows(idx[1], t.tn[0], t.tn[1], (int)sx, (int)sy, t.xwin);
+    t.xp = chp::interp_pattern(idx[0], t.tn[0], (int)sx, 4);
+    t.yp = chp::interp_pattern(idx[1], t.tn[1], (int)sy, chk::MARCH_BAND);
+    const size_t es = precision == CH_FP64 ? 8 : 4;
+    if (!chp::march_taken(es, t.rm, t.xp, t.yp, chp::march_shape(es, sx, t.tn), sx, t.tn,
+                          chp::interp_piped(es, t.rmax, sx)))
+        t.rm = 0;
     std::vector<int> iy0;
     for (int64_t j = 0; j < t.tn[1]; ++j) iy0.push_back(idx[1][4 * j]);
     bool good = true;
@@ -1604,25 +1540,6 @@ ch_status ch_batch_drops(ch_batch* b, int box, double threshold, int64_t cap, in
     return drops(b->e, box, threshold, cap, ndrops, root, cells);
 }
 
-// Where the own transforms take the place of hipFFT's (times of a solve, hipFFT's
-// first).  Periodic z: everywhere (512^3 FP32 2619 -> 1296 us, 300^3 FP64 1144 ->
-// 525, 240 x 180 x 160 FP64 205 -> 145, 32^3 FP32 35 -> 31) but for short rows
-// over many lines (32 x 128 x 128 FP64 46 -> 49 us, 30 x 128 x 100 FP32 36 -> 40:
-// threads and column tiles mostly masked).  Walls in FP64: large planes
-// (1024 x 1024 x 16 509 -> 402 us, 384 x 384 x 64 251 -> 193, 256^3 301 -> 293);
-// smaller ones are better off with hipFFT's fewer launches (128^3 71 -> 80,
-// 180 x 240 x 100 92 -> 105, 256 x 256 x 64 95 -> 98).  Walls in FP32 stay with
-// hipFFT (512^3: 1880 against 1290 us): after a step the mean mode of the next
-// right-hand side is what rounding left, which the solve along z amplifies by up
-// to nz^2, and other sums, no further from the truth, move a second step's P by
-// up to 4e-5 of it.
-static bool own_transforms(int nx, int ny, int nz, bool walls, int precision)
-{
-    const int64_t plane = (int64_t)nx * ny;
-    if (walls) return precision == CH_FP64 && plane >= 65536 && plane * nz >= 4194304;
-    return nx >= 36 || ny < 64;
-}
-
 static void poisson_free(ch_poisson* p)
 {
     if (p->have_fwd) (void)hipfftDestroy(p->fwd);
@@ -1660,7 +1577,7 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     if (p->nxp >= 16 && (double)padded * p->ny * p->nz < 2147483647.0) p->nxp = padded;
     const size_t nm = (size_t)p->ny * p->nxp;
     const int ext[3] = {p->nx, p->ny, p->nz};
-    p->own = own_transforms(p->nx, p->ny, p->nz, p->zwalls != 0, precision);
+    p->own = chp::own_transforms(p->nx, p->ny, p->nz, p->zwalls != 0, precision);
     for (int d = 0; d < (p->zwalls ? 2 : 3); ++d)
         p->own = chk::fft_radices(ext[d], precision == CH_FP32, &p->line[d]) && p->own;
     const hipfftType tf = precision == CH_FP64 ? HIPFFT_D2Z : HIPFFT_R2C;
