@@ -92,7 +92,6 @@ struct Engine {
     double* d_partial = nullptr;
     double* d_h3 = nullptr;
     double* d_mass = nullptr;
-    double* h_mass = nullptr;   // pinned (nbox): the masses come back in one copy
     int* d_flags = nullptr;
     hipStream_t stream = nullptr;
     int device = 0;
@@ -136,7 +135,6 @@ void free_engine(Engine& e)
     for (void* p : bufs)
         if (p) (void)hipFree(p);
     if (e.h_list) (void)hipHostFree(e.h_list);
-    if (e.h_mass) (void)hipHostFree(e.h_mass);
 }
 
 ch_status init_engine(Engine& e, int nbox, const ch_grid* g, const double* Cn, const double* Pe,
@@ -648,6 +646,7 @@ ch_status run_steps(Engine& e, const void* u, const void* v, const void* w, doub
 // Drop lists: ints before the drops (two counters), and the drops that come
 // back with the counters in one copy.
 constexpr int DROPS_HEAD = 2, DROPS_SOON = 1024;
+constexpr int H_LIST_INTS = DROPS_HEAD + 2 * DROPS_SOON;   // h_list
 
 // Drops of box `box`: labels, counts and the sorted (root, cells) list.
 ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, int64_t* root,
@@ -673,7 +672,7 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
         }
         e.lab_n = n;
     }
-    if (!e.h_list && hipHostMalloc((void**)&e.h_list, sizeof(int) * (DROPS_HEAD + 2 * DROPS_SOON),
+    if (!e.h_list && hipHostMalloc((void**)&e.h_list, sizeof(int) * H_LIST_INTS,
                                    hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         e.h_list = nullptr;
@@ -707,7 +706,7 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
         if (err != hipSuccess)
             return fail(CH_EHIP, "drop labelling failed: %s", hipGetErrorString(err));
         // the counters and the first drops in one copy
-        HIP_TRY(hipMemcpyAsync(e.h_list, e.d_list, sizeof(int) * (DROPS_HEAD + 2 * DROPS_SOON),
+        HIP_TRY(hipMemcpyAsync(e.h_list, e.d_list, sizeof(int) * H_LIST_INTS,
                                hipMemcpyDeviceToHost, e.stream));
         HIP_TRY(hipStreamSynchronize(e.stream));
         if (e.h_list[0] <= e.list_cap) {
@@ -851,12 +850,11 @@ ch_status mass(Engine& e, double* out)
         : chk::launch_mass<float>(e.P.nmblk, e.P.nbox, e.stream, e.d_boxes, e.C, e.d_partial,
                                   e.d_h3, e.d_mass);
     if (err != hipSuccess) return fail(CH_EHIP, "mass kernel failed: %s", hipGetErrorString(err));
-    if (!e.h_mass && hipHostMalloc((void**)&e.h_mass, sizeof(double) * e.P.nbox,
-                                   hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        e.h_mass = nullptr;   // the copy goes straight to the caller's array
-    }
-    double* dst = e.h_mass ? e.h_mass : out;
+    // through the pinned list that a labelling has left, if there is one and it
+    // holds them (47 us a call against 55 straight into the caller's array);
+    // pinned memory for the masses alone would cost a handle's first call more
+    // (59 -> 82 us) than a program that asks now and then gets back
+    double* dst = e.h_list && e.P.nbox <= H_LIST_INTS / 2 ? (double*)e.h_list : out;
     HIP_TRY(hipMemcpyAsync(dst, e.d_mass, sizeof(double) * e.P.nbox, hipMemcpyDeviceToHost,
                            e.stream));
     HIP_TRY(hipStreamSynchronize(e.stream));
