@@ -1092,16 +1092,26 @@ k_ccl_merge(int* lab, int nx, int ny, int nz, int px, int py, int pz, int gx, in
 }
 
 // The cells of every tile root that has been linked under another root go to
-// that root (only final roots are added to).
+// that root (only final roots are added to).  Each thread shortens its own
+// label's chain as it climbs (its label's label takes the label's place), so
+// that the threads of one long drop climb in strides that double: with plain
+// climbing a line of 10^6 cells in one drop, a chain of 15625 tile roots, took
+// 220-440 us.
 __global__ void __launch_bounds__(256)
-k_ccl_sum(const int* __restrict__ lab, int* __restrict__ cnt, const int* __restrict__ meta,
+k_ccl_sum(int* __restrict__ lab, int* __restrict__ cnt, const int* __restrict__ meta,
           const int* __restrict__ list, int cap)
 {
+    constexpr int DEV = __HIP_MEMORY_SCOPE_AGENT;
     const int n = meta[0] < cap ? meta[0] : cap;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
         const int r = list[e];
         int root = lab[r];
-        while (lab[root] != root) root = lab[root];
+        // labels only decrease along the chain, and a label read while its
+        // owner shortens it is an ancestor either way: it ends at the root
+        for (int up = ccl_load<DEV>(lab, root); up != root; up = ccl_load<DEV>(lab, root)) {
+            root = up;
+            __hip_atomic_store(lab + r, root, __ATOMIC_RELAXED, DEV);
+        }
         if (root != r) atomicAdd(cnt + root, cnt[r]);
     }
 }

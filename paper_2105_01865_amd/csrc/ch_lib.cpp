@@ -680,7 +680,9 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
     }
     const size_t es = chp::esize(e.P.prec);
     const void* C = (const char*)e.C + d.c_off * es;
-    const int bc[3] = {d.bc[0], d.bc[1], d.bc[2]};
+    const int dn[3] = {d.n[0], d.n[1], d.n[2]}, dbc[3] = {d.bc[0], d.bc[1], d.bc[2]};
+    int m[3], bc[3];
+    chp::drop_axes(dn, dbc, m, bc);
     // the list of tile roots: sized from a first pass if the cached one is too short
     int64_t want = std::max<int64_t>(std::max<int64_t>(e.list_cap, DROPS_SOON), n / 256);
     for (int pass = 0; pass < 2; ++pass) {
@@ -699,9 +701,9 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
         int* list = out + 2 * e.list_cap;
         HIP_TRY(hipMemsetAsync(meta, 0, sizeof(int) * DROPS_HEAD, e.stream));
         const hipError_t err = e.P.prec == CH_FP64
-            ? chk::launch_drops<double>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab,
+            ? chk::launch_drops<double>(e.stream, C, m[0], m[1], m[2], bc, thr, e.d_lab,
                                         e.d_cnt, meta, list, (int)e.list_cap, out)
-            : chk::launch_drops<float>(e.stream, C, d.n[0], d.n[1], d.n[2], bc, thr, e.d_lab,
+            : chk::launch_drops<float>(e.stream, C, m[0], m[1], m[2], bc, thr, e.d_lab,
                                        e.d_cnt, meta, list, (int)e.list_cap, out);
         if (err != hipSuccess)
             return fail(CH_EHIP, "drop labelling failed: %s", hipGetErrorString(err));
