@@ -675,9 +675,10 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
     if (!e.h_list && hipHostMalloc((void**)&e.h_list, sizeof(int) * H_LIST_INTS,
                                    hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        e.h_list = nullptr;
-        return fail(CH_ENOMEM, "cannot allocate the drop list");
+        e.h_list = nullptr;   // pageable memory of this call instead
     }
+    std::vector<int> pageable(e.h_list ? 0 : H_LIST_INTS);
+    int* const head = e.h_list ? e.h_list : pageable.data();
     const size_t es = chp::esize(e.P.prec);
     const void* C = (const char*)e.C + d.c_off * es;
     const int dn[3] = {d.n[0], d.n[1], d.n[2]}, dbc[3] = {d.bc[0], d.bc[1], d.bc[2]};
@@ -708,15 +709,15 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
         if (err != hipSuccess)
             return fail(CH_EHIP, "drop labelling failed: %s", hipGetErrorString(err));
         // the counters and the first drops in one copy
-        HIP_TRY(hipMemcpyAsync(e.h_list, e.d_list, sizeof(int) * H_LIST_INTS,
+        HIP_TRY(hipMemcpyAsync(head, e.d_list, sizeof(int) * H_LIST_INTS,
                                hipMemcpyDeviceToHost, e.stream));
         HIP_TRY(hipStreamSynchronize(e.stream));
-        if (e.h_list[0] <= e.list_cap) {
-            const int found = e.h_list[1];
+        if (head[0] <= e.list_cap) {
+            const int found = head[1];
             std::vector<std::pair<int, int>> r(found);
             if (found <= DROPS_SOON) {
                 if (found > 0)
-                    memcpy((void*)r.data(), e.h_list + DROPS_HEAD, sizeof(int) * 2 * found);
+                    memcpy((void*)r.data(), head + DROPS_HEAD, sizeof(int) * 2 * found);
             } else {
                 HIP_TRY(hipMemcpy((void*)r.data(), out, sizeof(int) * 2 * found,
                                   hipMemcpyDeviceToHost));
@@ -729,7 +730,7 @@ ch_status drops(Engine& e, int box, double thr, int64_t cap, int64_t* ndrops, in
             *ndrops = found;
             return CH_OK;
         }
-        want = e.h_list[0];
+        want = head[0];
     }
     return fail(CH_EHIP, "drop list did not settle");
 }
