@@ -1294,13 +1294,16 @@ k_press_rhs(PressTile tile, PressArgs a, const T* __restrict__ C, const T* __res
 // scratch, of which one per block of PK rows is used.  The result is scaled by
 // `scale` (the inverse transform's 1 / (nx ny)).
 //
-// What bounds it: with four waves per SIMD (512^3) each wave's chain of blocks
-// of PK rows, so the next block's loads go out before this block's rows are
-// eliminated.  The mean mode is one serial chain over all of z, its loads
-// behind its stores; it has a work-group of its own (press_mean) that stages z
-// through LDS.  512^3 FP32: 430-439 us against 707 with the mean mode in a lane
-// of a wave and each block's loads after the one before (the spectrum read and
-// written twice at a copy's rate: 440).
+// What bounds it: each wave's chain of blocks of PK rows, so the next block's
+// loads go out before this block's rows are eliminated; on large planes the
+// bytes.  The mean mode is one serial chain over all of z, its loads behind its
+// stores; it has a work-group of its own (press_mean) that stages z through LDS.
+// 512^3 FP32: 433 us against 677-706 with the mean mode in a lane of a wave and
+// each block's loads after the one before (the spectrum read and written twice at
+// a copy's rate: 440), FP64 983 against 1183.  Two forms, one arithmetic: LONG
+// forms the rows' addresses in 64 bits (236 VGPRs in single, 179 in double
+// precision, 2 waves per SIMD); the other counts elements in 32 bits (127 and
+// 117, 4 waves), which planes of many modes and few rows need (launch_press_solve).
 template <typename T>
 struct Cplx;
 template <>
@@ -1384,8 +1387,8 @@ __device__ void press_mean(T* __restrict__ fs, int64_t s2, int nz, T h2, T sc)
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, bool LONG>
+__global__ void __launch_bounds__(256, LONG ? 1 : 4)
 k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, int nxp, double h,
             double scale)
 {
@@ -1397,7 +1400,8 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
         press_mean<T>(spec, 2 * nm, nz, T(h * h), sc);
         return;
     }
-    const int64_t ngroups = (nm + 31) / 32;
+    const int nmi = (int)nm;                        // (fewer than 2^31 elements in all)
+    const int ngroups = (nmi + 31) / 32;
     const double PI = 3.14159265358979323846;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5;
@@ -1406,31 +1410,35 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
     const int lmin = nz - 1 - M;                    // ... by the lane with fewer (M or M - 1)
     const T ih2 = T(1.0 / (h * h));
     constexpr int PK = sizeof(T) == 4 ? 8 : 4;      // rows per block
-    const int64_t wave0 = ((int64_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x) >> 6;
-    const int64_t nwaves = ((int64_t)(gridDim.x - 1) * blockDim.x) >> 6;
+    const int wave0 = (int)((blockIdx.x - 1) * (blockDim.x >> 6) + (threadIdx.x >> 6));
+    const int nwaves = (int)((gridDim.x - 1) * (blockDim.x >> 6));
     // the group loop is uniform over a wave: every lane reaches the exchange
-    for (int64_t g = wave0; g < ngroups; g += nwaves) {
-        const int64_t m = g * 32 + (lane & 31);
-        const int j = (int)(m / nxp), i = (int)(m - (int64_t)j * nxp);
-        const bool on = m < nm && i < nxh && m != 0;   // m = 0 is the mean mode
-        const int64_t mm = on ? m : 0;
+    for (int g = wave0; g < ngroups; g += nwaves) {
+        const uint32_t m = (uint32_t)g * 32 + (lane & 31);
+        const int j = (int)(m / (uint32_t)nxp), i = (int)(m - (uint32_t)j * nxp);
+        const bool on = m < (uint32_t)nmi && i < nxh && m != 0;   // m = 0 is the mean mode
+        const int mm = on ? (int)m : 0;
         const double sx = sin(PI * i / nx), sy = sin(PI * j / ny);
         const T lxy = T(-4.0 / (h * h) * (sx * sx + sy * sy));
-        // row s of the lane's half at f + s * st, its scratch at ck + s * ct
-        const int64_t ct = half == 0 ? nm : -nm, st = ct;
-        V* const fm = reinterpret_cast<V*>(spec) + mm;
-        V* const f = fm + (half == 0 ? 0 : (nz - 1) * nm);
-        T* const ck = cp + mm + (half == 0 ? 0 : (nz - 1) * nm);
+        // row s of the lane's half in spec and cp: LONG, at strides of its own from
+        // the half's end; else by 32-bit element numbers, with half the registers
+        const int64_t st = half == 0 ? nm : -nm;
+        const int e0 = mm + (half == 0 ? 0 : (nz - 1) * nmi), de = half == 0 ? nmi : -nmi;
+        V* const f = reinterpret_cast<V*>(spec);
+        V* const fl = f + mm + (half == 0 ? 0 : (nz - 1) * nm);
+        T* const cl = cp + mm + (half == 0 ? 0 : (nz - 1) * nm);
+        auto fat = [&](int s) -> V& { return LONG ? fl[s * st] : f[(uint32_t)(e0 + s * de)]; };
+        auto cat = [&](int s) -> T& { return LONG ? cl[s * st] : cp[(uint32_t)(e0 + s * de)]; };
         auto diag = [&](int s) { return lxy - (s == 0 ? ih2 : T(2) * ih2); };   // a half's row s
         // a block's rows (past the half's end its last row again)
         auto load = [&](int s0, V* v) {
-            if (s0 + PK <= lmin) {
-                const V* p = f + s0 * st;
+            if (LONG && s0 + PK <= lmin) {
+                const V* p = fl + s0 * st;
 #pragma unroll
                 for (int q = 0; q < PK; ++q) v[q] = p[q * st];
             } else {
 #pragma unroll
-                for (int q = 0; q < PK; ++q) v[q] = f[(s0 + q < len ? s0 + q : len - 1) * st];
+                for (int q = 0; q < PK; ++q) v[q] = fat(s0 + q < len ? s0 + q : len - 1);
             }
         };
         // elimination towards row M in blocks of PK rows: d into f, and into
@@ -1441,11 +1449,11 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
             V nv[PK];
             load(0, nv);
             for (int s0 = 0; s0 < len; s0 += PK) {
-                ck[s0 * ct] = c;
+                cat(s0) = c;
                 V fv[PK];
 #pragma unroll
                 for (int q = 0; q < PK; ++q) fv[q] = nv[q];
-                load(s0 + PK < len ? s0 + PK : s0, nv);
+                if (s0 + PK < len) load(s0 + PK, nv);
 #pragma unroll
                 for (int q = 0; q < PK; ++q) {
                     const int sq = s0 + q;
@@ -1457,7 +1465,7 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
                     V o;
                     o.x = dr;
                     o.y = di;
-                    f[sq * st] = o;
+                    fat(sq) = o;
                 }
             }
         }
@@ -1465,7 +1473,7 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
         // coefficients (zero for an empty half), across the wave
         T fmr = T(0), fmi = T(0);
         if (on && half == 0) {
-            const V v = fm[M * nm];
+            const V v = f[mm + M * nmi];
             fmr = v.x;
             fmi = v.y;
         }
@@ -1484,7 +1492,7 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
                 V o;
                 o.x = xr * sc;
                 o.y = xi * sc;
-                fm[M * nm] = o;
+                f[mm + M * nmi] = o;
             }
             // back substitution from row M outwards, block by block: the
             // block's c again from its checkpoint (the same operations as on
@@ -1493,16 +1501,17 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
                 V nv[PK];
                 int s0 = (len - 1) / PK * PK;
                 load(s0, nv);
-                T cnext = ck[s0 * ct];
+                T cnext = cat(s0);
                 for (; s0 >= 0; s0 -= PK) {
                     V fv[PK];
                     T cc[PK];
                     T cin = cnext;
 #pragma unroll
                     for (int q = 0; q < PK; ++q) fv[q] = nv[q];
-                    const int sn = s0 >= PK ? s0 - PK : 0;
-                    load(sn, nv);
-                    cnext = ck[sn * ct];
+                    if (s0 >= PK) {
+                        load(s0 - PK, nv);
+                        cnext = cat(s0 - PK);
+                    }
 #pragma unroll
                     for (int q = 0; q < PK; ++q) {
                         cc[q] = T(0);
@@ -1520,7 +1529,7 @@ k_press_tri(T* __restrict__ spec, T* __restrict__ cp, int nx, int ny, int nz, in
                         V o;
                         o.x = xr * sc;
                         o.y = xi * sc;
-                        f[sq * st] = o;
+                        fat(sq) = o;
                     }
                 }
             }
@@ -1930,8 +1939,15 @@ hipError_t launch_press_solve(hipStream_t st, int zwalls, void* spec, void* cp, 
     if (zwalls) {
         // one work-group for the mean mode, one wave per 32 modes (two lanes per mode)
         const int64_t nm = (int64_t)ny * nxp;
-        hipLaunchKernelGGL((k_press_tri<T>), dim3(grid_for((nm + 31) / 32 * 64) + 1), dim3(256), 0,
-                           st, (T*)spec, (T*)cp, nx, ny, nz, nxp, h, 1.0 / ((double)nx * ny));
+        // The form by the rows (us, one of 2 waves per SIMD first): FP32 1024^2
+        // planes of 8 rows 44 / 28 (before either 28), 16 rows 55 / 41 (43), 64
+        // rows 190 / 179; 512^2 of 16 19 / 14, 32 28 / 22, 128 93 / 92, 256 203 /
+        // 219, 512 434 / 452.  FP64 1024^2 of 8 42 / 35, 32 183 / 184; 512^2 of 32
+        // 39.5 / 44.6, 64 87 / 89, 256 414 / 459.
+        const auto k = (sizeof(T) == 8 ? nz >= 32 : nz >= 192) ? k_press_tri<T, true>
+                                                               : k_press_tri<T, false>;
+        hipLaunchKernelGGL(k, dim3(grid_for((nm + 31) / 32 * 64) + 1), dim3(256), 0, st, (T*)spec,
+                           (T*)cp, nx, ny, nz, nxp, h, 1.0 / ((double)nx * ny));
     } else {
         const int64_t n = (int64_t)nz * ny * (nx / 2 + 1);
         const double* sy = sines + (nx / 2 + 1);
