@@ -997,13 +997,7 @@ struct ch_poisson {
     bool have_fwd = false, have_inv = false;
     void* phat = nullptr;   // 2 P^l - P^{l-1}
     void* rhs = nullptr;    // eq-newpoi right-hand side
-    // Row pitch of the spectrum, complex elements: nx/2 + 1, from 16 on rounded
-    // up to a multiple of 8 (below, the padding would be a third of a row and
-    // the transforms take a few us), so that rows start on 64 bytes (128 in
-    // double).  With the
-    // bare nx/2 + 1 (257 at nx = 512) every row starts elsewhere in a cache
-    // line, which costs the column transforms: 512^3 FP32 forward 807 -> 622 us
-    // (FP64 1084 -> 873), 256^3 88 -> 61 us (123 -> 87).
+    // row pitch of the spectrum, complex elements (spectrum_pitch)
     int nxp = 0;
     void* spec = nullptr;   // its transform, nz x ny x nxp complex
     void* cp = nullptr;     // walls: Thomas scratch, nz x ny x nxp reals
@@ -1573,14 +1567,10 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     p->prec = precision;
     const size_t es = precision == CH_FP64 ? 8 : 4;
     const size_t n = (size_t)p->nx * p->ny * p->nz;
-    p->nxp = p->nx / 2 + 1;
-    const int padded = (p->nxp + 7) / 8 * 8;
-    if (p->nxp >= 16 && (double)padded * p->ny * p->nz < 2147483647.0) p->nxp = padded;
-    const size_t nm = (size_t)p->ny * p->nxp;
     const int ext[3] = {p->nx, p->ny, p->nz};
-    p->own = chp::own_transforms(p->nx, p->ny, p->nz, p->zwalls != 0, precision);
-    for (int d = 0; d < (p->zwalls ? 2 : 3); ++d)
-        p->own = chk::fft_radices(ext[d], precision == CH_FP32, &p->line[d]) && p->own;
+    p->own = chp::own_lines(ext, p->zwalls != 0, precision, p->line);
+    p->nxp = chp::spectrum_pitch(p->nx, p->ny, p->nz, p->own);
+    const size_t nm = (size_t)p->ny * p->nxp;
     const hipfftType tf = precision == CH_FP64 ? HIPFFT_D2Z : HIPFFT_R2C;
     const hipfftType ti = precision == CH_FP64 ? HIPFFT_Z2D : HIPFFT_C2R;
     // z walls: 2-D transforms of the planes; periodic z: one 3-D transform

@@ -200,6 +200,23 @@ inline bool march_taken(size_t esize, int rm, int xp, int yp, const MarchShape& 
     return esize == 4 ? !piped || tn[0] * tn[1] * tn[2] < (1 << 25) : sx <= 128;
 }
 
+// Row pitch of the pressure solve's spectrum in complex elements, at least nx/2 +
+// 1.  Rounded up to a multiple of 8 rows start on 64 bytes (128 in double); with
+// the bare nx/2 + 1 (257 at nx = 512) every row starts elsewhere in a cache line,
+// which costs the column transforms: the library's 512^3 FP32 forward 807 -> 622
+// us (FP64 1084 -> 873), a solve between walls at 128^3 FP64 77 -> 71, 100^3 67 ->
+// 60.  Our own transforms take it from 16 elements on.  For the library's, rows of
+// 96 to 1024 points: shorter ones lose its plans of small meshes (periodic 32 x
+// 64 x 64 FP32 26 us bare, 40 padded; walls 32 x 16 x 16 20.5 and 25.5), longer
+// ones gain nothing and lose along z (2048 x 2048 x 32 walls FP32 2180 bare, 2380
+// padded, FP64 3860 and 4110).
+inline int spectrum_pitch(int nx, int ny, int nz, bool own)
+{
+    const int bare = nx / 2 + 1, padded = (bare + 7) / 8 * 8;
+    const bool pad = own ? bare >= 16 : nx >= 96 && nx <= 1024;
+    return pad && (double)padded * ny * nz < 2147483647.0 ? padded : bare;
+}
+
 // Where the own transforms take the place of hipFFT's (times of a solve, hipFFT's
 // first).  Periodic z: everywhere (512^3 FP32 2619 -> 1296 us, 300^3 FP64 1144 ->
 // 525, 240 x 180 x 160 FP64 205 -> 145, 32^3 FP32 35 -> 31) but for short rows
@@ -217,6 +234,16 @@ inline bool own_transforms(int nx, int ny, int nz, bool walls, int precision)
     const int64_t plane = (int64_t)nx * ny;
     if (walls) return precision == CH_FP64 && plane >= 65536 && plane * nz >= 4194304;
     return nx >= 36 || ny < 64;
+}
+
+// Whether a solve takes the own transforms, and the passes of their lines (two
+// axes between walls).
+inline bool own_lines(const int n[3], bool walls, int precision, chk::FftLine line[3])
+{
+    bool own = own_transforms(n[0], n[1], n[2], walls, precision);
+    for (int d = 0; d < (walls ? 2 : 3); ++d)
+        own = chk::fft_radices(n[d], precision == CH_FP32, &line[d]) && own;
+    return own;
 }
 
 }  // namespace chp
