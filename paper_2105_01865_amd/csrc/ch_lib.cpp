@@ -1569,7 +1569,7 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     const size_t n = (size_t)p->nx * p->ny * p->nz;
     const int ext[3] = {p->nx, p->ny, p->nz};
     p->own = chp::own_lines(ext, p->zwalls != 0, precision, p->line);
-    p->nxp = chp::spectrum_pitch(p->nx, p->ny, p->nz, p->own);
+    p->nxp = chp::spectrum_pitch(p->nx, p->ny, p->nz, p->zwalls != 0, p->own);
     const size_t nm = (size_t)p->ny * p->nxp;
     const hipfftType tf = precision == CH_FP64 ? HIPFFT_D2Z : HIPFFT_R2C;
     const hipfftType ti = precision == CH_FP64 ? HIPFFT_Z2D : HIPFFT_C2R;

@@ -206,14 +206,17 @@ inline bool march_taken(size_t esize, int rm, int xp, int yp, const MarchShape& 
 // which costs the column transforms: the library's 512^3 FP32 forward 807 -> 622
 // us (FP64 1084 -> 873), a solve between walls at 128^3 FP64 77 -> 71, 100^3 67 ->
 // 60.  Our own transforms take it from 16 elements on.  For the library's, rows of
-// 96 to 1024 points: shorter ones lose its plans of small meshes (periodic 32 x
-// 64 x 64 FP32 26 us bare, 40 padded; walls 32 x 16 x 16 20.5 and 25.5), longer
-// ones gain nothing and lose along z (2048 x 2048 x 32 walls FP32 2180 bare, 2380
-// padded, FP64 3860 and 4110).
-inline int spectrum_pitch(int nx, int ny, int nz, bool own)
+// 96 to 1024 points between walls or of more than 2^20 cells: small periodic
+// meshes and short rows lose its plans for them (periodic 32 x 64 x 64 FP32 26 us
+// bare, 40 padded; walls 32 x 16 x 16 20.5 and 25.5), longer rows gain nothing and
+// lose along z (2048 x 2048 x 32 walls FP32 2180 bare, 2380 padded, FP64 3860 and
+// 4110).
+inline int spectrum_pitch(int nx, int ny, int nz, bool walls, bool own)
 {
     const int bare = nx / 2 + 1, padded = (bare + 7) / 8 * 8;
-    const bool pad = own ? bare >= 16 : nx >= 96 && nx <= 1024;
+    const bool pad = own ? bare >= 16
+                         : nx >= 96 && nx <= 1024 &&
+                               (walls || (int64_t)nx * ny * nz > (1 << 20));
     return pad && (double)padded * ny * nz < 2147483647.0 ? padded : bare;
 }
 
@@ -221,7 +224,10 @@ inline int spectrum_pitch(int nx, int ny, int nz, bool own)
 // first).  Periodic z: everywhere (512^3 FP32 2619 -> 1296 us, 300^3 FP64 1144 ->
 // 525, 240 x 180 x 160 FP64 205 -> 145, 32^3 FP32 35 -> 31) but for short rows
 // over many lines (32 x 128 x 128 FP64 46 -> 49 us, 30 x 128 x 100 FP32 36 -> 40:
-// threads and column tiles mostly masked).  Walls in FP64: large planes
+// threads and column tiles mostly masked) and for small meshes of powers of two
+// with few rows along y and long lines along z (16 x 16 x 256 FP32 26 -> 33, 128 x
+// 16 x 128 FP32 29 -> 36.5, FP64 32 -> 37, 256 x 16 x 256 59 -> 63; 256 x 32 x 256
+// 84 -> 78: few work-groups, and the library's shortest plans).  Walls in FP64: large planes
 // (1024 x 1024 x 16 509 -> 402 us, 384 x 384 x 64 251 -> 193, 256^3 301 -> 293);
 // smaller ones are better off with hipFFT's fewer launches (128^3 71 -> 80,
 // 180 x 240 x 100 92 -> 105, 256 x 256 x 64 95 -> 98).  Walls in FP32 stay with
@@ -233,6 +239,8 @@ inline bool own_transforms(int nx, int ny, int nz, bool walls, int precision)
 {
     const int64_t plane = (int64_t)nx * ny;
     if (walls) return precision == CH_FP64 && plane >= 65536 && plane * nz >= 4194304;
+    const bool p2 = ((nx & (nx - 1)) | (ny & (ny - 1)) | (nz & (nz - 1))) == 0;
+    if (p2 && ny <= 32 && nz >= 64 && plane * nz <= (1 << 20)) return false;
     return nx >= 36 || ny < 64;
 }
 

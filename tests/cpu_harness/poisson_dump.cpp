@@ -13,7 +13,7 @@ int main()
     while (scanf("%d %d %d %d %d", n, n + 1, n + 2, &walls, &prec) == 5) {
         chk::FftLine line[3] = {};
         const bool own = chp::own_lines(n, walls != 0, prec, line);
-        printf("%d %d", own ? 1 : 0, chp::spectrum_pitch(n[0], n[1], n[2], own));
+        printf("%d %d", own ? 1 : 0, chp::spectrum_pitch(n[0], n[1], n[2], walls != 0, own));
         for (int d = 0; d < 3; ++d) {
             printf(" %d", line[d].passes);
             for (int p = 0; p < line[d].passes; ++p) printf(" %d", line[d].radix[p]);

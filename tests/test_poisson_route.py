@@ -75,3 +75,19 @@ def test_radices_multiply_to_the_length_and_the_twiddle_index_stays_in_range():
                 j = np.arange(n // R, dtype=np.uint64)
                 assert np.array_equal((j * inv) >> 20, j // s)
                 s *= R
+
+
+@pytest.mark.parametrize("shape,walls,own64,own32", [
+    ((160, 180, 240), 0, True, True), ((32, 32, 32), 0, True, True), ((36, 64, 36), 0, True, True),
+    ((100, 128, 30), 0, False, False),                                   # short rows, many lines
+    ((128, 16, 128), 0, False, False), ((256, 16, 16), 0, False, False),  # small, powers of two
+    ((256, 16, 256), 0, False, False), ((64, 8, 512), 0, False, False),
+    ((256, 32, 256), 0, True, True), ((64, 64, 64), 0, True, True), ((120, 16, 128), 0, True, True),
+    ((32, 16, 128), 0, True, True),
+    ((28, 28, 28), 0, False, False), ((64, 64, 2048), 0, False, False),   # lengths it does not take
+    ((256, 256, 256), 1, True, False), ((64, 128, 128), 1, False, False)])
+def test_own_transforms_or_the_library(shape, walls, own64, own32):
+    got = route([(shape, walls, p) for p in (0, 1)])
+    assert [g[0] for g in got] == [own64, own32]
+    if not walls and not got[0][0] and np.prod(shape) <= 1 << 20:
+        assert all(g[1] == shape[2] // 2 + 1 for g in got)
