@@ -415,7 +415,7 @@ static hipError_t fft_shape(int n, Go&& go)
     if (n <= 256) return go(IC<8>{}, IC<256>{});
     if (n <= 512) return go(IC<8>{}, IC<512>{});
     if constexpr (sizeof(T) == 8) return go(IC<8>{}, IC<1024>{});
-    return go(IC<4>{}, IC<512>{});
+    else return go(IC<4>{}, IC<512>{});
 }
 // Row shapes (pairs of rows, points per thread, threads).  Four pairs of FP32
 // (eight: 1468 us for the same work, four: 1389), and of FP64, there with half

@@ -91,3 +91,15 @@ def test_own_transforms_or_the_library(shape, walls, own64, own32):
     assert [g[0] for g in got] == [own64, own32]
     if not walls and not got[0][0] and np.prod(shape) <= 1 << 20:
         assert all(g[1] == shape[2] // 2 + 1 for g in got)
+
+
+def test_only_launched_shapes_of_columns_are_built():
+    """Column kernels in double precision have tiles of eight columns: a tile of
+    four is for single precision's lines of over 512 points."""
+    lib = os.path.join(ROOT, "paper_2105_01865_amd", "libch.so")
+    if not os.path.exists(lib):
+        pytest.skip("libch.so not built")
+    out = subprocess.run(["nm", "-C", lib], capture_output=True, text=True, check=True).stdout
+    cols = [ln for ln in out.splitlines() if "k_fft_cols<" in ln or "k_fft_zsolve<" in ln]
+    assert any("float, 4, 8, 512" in ln for ln in cols)
+    assert not any("double, 4," in ln for ln in cols)
