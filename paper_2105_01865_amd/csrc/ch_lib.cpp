@@ -1603,13 +1603,7 @@ ch_status ch_poisson_create(const ch_grid* g, int z_walls, int precision, ch_poi
     }
     if (p->own)
         for (int d = 0; d < (p->zwalls ? 2 : 3); ++d) {
-            std::vector<double> w(2 * (size_t)ext[d]);
-            for (int m = 0; m < ext[d]; ++m) {
-                const double a = -2.0 * M_PI * m / ext[d];
-                w[2 * m] = std::cos(a);
-                w[2 * m + 1] = std::sin(a);
-            }
-            if (!upload_weights(&p->tw[d], w, precision)) {
+            if (!upload_weights(&p->tw[d], chp::fft_twiddles(ext[d]), precision)) {
                 poisson_free(p);
                 return fail(CH_ENOMEM, "cannot allocate the pressure work arrays");
             }

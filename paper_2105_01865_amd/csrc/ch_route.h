@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "../../include/ch.h"
@@ -252,6 +253,21 @@ inline bool own_lines(const int n[3], bool walls, int precision, chk::FftLine li
     for (int d = 0; d < (walls ? 2 : 3); ++d)
         own = chk::fft_radices(n[d], precision == CH_FP32, &line[d]) && own;
     return own;
+}
+
+// Twiddles exp(-2 pi i m / n), m < n, as (re, im) pairs: formed in extended
+// precision and rounded once.  From an angle rounded to double they are off by up
+// to 4 units in the last place, which lines of 1000 points show (40 x 30 x 1000
+// periodic FP64, rms error of a solve 8.8e-16 instead of 5.5e-16 of the rms).
+inline std::vector<double> fft_twiddles(int n)
+{
+    const long double two_pi = 6.283185307179586476925286766559L;
+    std::vector<double> w(2 * (size_t)n);
+    for (int m = 0; m < n; ++m) {
+        w[2 * m] = (double)std::cos(two_pi * m / n);
+        w[2 * m + 1] = (double)-std::sin(two_pi * m / n);
+    }
+    return w;
 }
 
 }  // namespace chp
