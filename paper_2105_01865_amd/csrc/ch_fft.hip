@@ -5,7 +5,8 @@
 // work-group brings a tile of whole lines into LDS, transforms them there and
 // writes them back.
 //   rows     2 CW rows of reals as CW complex lines (one row in the real, the
-//            next in the imaginary parts), separated on the way out
+//            next in the imaginary parts), separated on the way out; in single
+//            precision rows of odd length one by one
 //   columns  CW neighbouring columns (64 or 128 bytes), in place
 //   z solve  the same along z, forward, divided by the Laplacian's eigenvalues,
 //            and back: the spectrum is read and written once for what would be
@@ -53,6 +54,33 @@ __device__ __forceinline__ CV<T> cmul(CV<T> a, CV<T> b)
 {
     return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
+// c x (+ c2 x2), the constants in single precision as two floats: rounded to one,
+// their error is the same in every butterfly and adds up (27^3 FP32 periodic, rms
+// error of a solve 2.0e-7 of the rms with one, 1.84e-7 with two; the library's
+// transforms 1.86e-7).
+__device__ __forceinline__ double cprod(double c, double x) { return c * x; }
+__device__ __forceinline__ float cprod(double c, float x)
+{
+    const float hi = (float)c, lo = (float)(c - hi);
+    return fmaf(hi, x, lo * x);
+}
+__device__ __forceinline__ double cprod(double c, double x, double c2, double x2)
+{
+    return c * x + c2 * x2;
+}
+__device__ __forceinline__ float cprod(double c, float x, double c2, float x2)
+{
+    const float hi = (float)c, lo = (float)(c - hi);
+    const float hi2 = (float)c2, lo2 = (float)(c2 - hi2);
+    return fmaf(hi, x, fmaf(hi2, x2, fmaf(lo, x, lo2 * x2)));
+}
+template <typename T>
+__device__ __forceinline__ CV<T> cprod(double c, CV<T> a) { return {cprod(c, a.x), cprod(c, a.y)}; }
+template <typename T>
+__device__ __forceinline__ CV<T> cprod(double c, CV<T> a, double c2, CV<T> b)
+{
+    return {cprod(c, a.x, c2, b.x), cprod(c, a.y, c2, b.y)};
+}
 template <typename T>
 __device__ __forceinline__ CV<T> times_mi(CV<T> a) { return {a.y, -a.x}; }   // -i a
 
@@ -65,8 +93,8 @@ __device__ __forceinline__ void dft(CV<T>* v)
         v[0] = a + b;
         v[1] = a - b;
     } else if constexpr (R == 3) {
-        const T c = T(0.86602540378443864676);   // sin(pi/3)
-        const CV<T> s = v[1] + v[2], d = times_mi(c * (v[1] - v[2]));
+        constexpr double c = 0.86602540378443864676;   // sin(pi/3)
+        const CV<T> s = v[1] + v[2], d = times_mi(cprod(c, v[1] - v[2]));
         const CV<T> t = v[0] - T(0.5) * s;
         v[0] = v[0] + s;
         v[1] = t + d;
@@ -79,11 +107,11 @@ __device__ __forceinline__ void dft(CV<T>* v)
         v[3] = b - d;
     } else if constexpr (R == 5) {
         // cosines and sines of 2 pi/5 and 4 pi/5
-        const T c1 = T(0.30901699437494742410), c2 = T(-0.80901699437494742410);
-        const T s1 = T(0.95105651629515357212), s2 = T(0.58778525229247312917);
+        constexpr double c1 = 0.30901699437494742410, c2 = -0.80901699437494742410;
+        constexpr double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;
         const CV<T> t1 = v[1] + v[4], t2 = v[2] + v[3], t3 = v[1] - v[4], t4 = v[2] - v[3];
-        const CV<T> m1 = v[0] + (c1 * t1 + c2 * t2), m2 = v[0] + (c2 * t1 + c1 * t2);
-        const CV<T> n1 = times_mi(s1 * t3 + s2 * t4), n2 = times_mi(s2 * t3 - s1 * t4);
+        const CV<T> m1 = v[0] + cprod(c1, t1, c2, t2), m2 = v[0] + cprod(c2, t1, c1, t2);
+        const CV<T> n1 = times_mi(cprod(s1, t3, s2, t4)), n2 = times_mi(cprod(s2, t3, -s1, t4));
         v[0] = v[0] + (t1 + t2);
         v[1] = m1 + n1;
         v[4] = m1 - n1;
@@ -319,26 +347,30 @@ k_fft_zsolve(FftLine f, CV<T>* __restrict__ spec, int ny, int nxh, int nxp, doub
     }
 }
 
-// Rows of reals to the half spectrum: 2 CW rows per group.
-template <bool P2, typename T, int CW, int VPT, int NT>
+// Rows of reals to the half spectrum.  PAIR: 2 CW rows per group, two in a line;
+// else CW rows, each a line's real parts (launch_fft_rows).
+template <bool P2, bool PAIR, typename T, int CW, int VPT, int NT>
 __global__ void __launch_bounds__(NT, 4)
 k_fft_rows(FftLine f, const T* __restrict__ in, CV<T>* __restrict__ out, int nxp, int64_t nrows)
 {
-    constexpr int RP = CW + 1;
+    constexpr int RP = CW + 1, ROWS = PAIR ? 2 * CW : CW;
     extern __shared__ __align__(16) unsigned char smem[];
     CV<T>* tw = reinterpret_cast<CV<T>*>(smem);
     CV<T>* L = tw + f.n;
     const int tid = threadIdx.x, n = f.n;
-    const int64_t row0 = (int64_t)blockIdx.x * (2 * CW);
-    const int nr = nrows - row0 < 2 * CW ? (int)(nrows - row0) : 2 * CW;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int nr = nrows - row0 < ROWS ? (int)(nrows - row0) : ROWS;
     Twiddles<T, NT> wt;
     wt.load(f, tid);
     for (int x = tid; x < n; x += NT) {
-        T v[2 * CW];
+        T v[ROWS];
 #pragma unroll
-        for (int r = 0; r < 2 * CW; ++r) v[r] = r < nr ? in[(row0 + r) * n + x] : T(0);
+        for (int r = 0; r < ROWS; ++r) v[r] = r < nr ? in[(row0 + r) * n + x] : T(0);
 #pragma unroll
-        for (int p = 0; p < CW; ++p) L[x * RP + p] = CV<T>{v[2 * p], v[2 * p + 1]};
+        for (int p = 0; p < CW; ++p) {
+            if constexpr (PAIR) L[x * RP + p] = CV<T>{v[2 * p], v[2 * p + 1]};
+            else L[x * RP + p] = CV<T>{v[p], T(0)};
+        }
     }
     wt.store(tw, f, tid);
     fft_tile<P2, T, CW, RP, VPT, NT>(L, tw, f, tid);
@@ -347,46 +379,56 @@ k_fft_rows(FftLine f, const T* __restrict__ in, CV<T>* __restrict__ out, int nxp
         const int m = k == 0 ? 0 : n - k;
 #pragma unroll
         for (int p = 0; p < CW; ++p) {
-            if (2 * p >= nr) break;
-            const CV<T> a = L[k * RP + p], b = L[m * RP + p];
-            CV<T>* o = out + (row0 + 2 * p) * nxp + k;
-            o[0] = CV<T>{T(0.5) * (a.x + b.x), T(0.5) * (a.y - b.y)};
-            if (2 * p + 1 < nr) o[nxp] = CV<T>{T(0.5) * (a.y + b.y), T(0.5) * (b.x - a.x)};
+            if constexpr (PAIR) {
+                if (2 * p >= nr) break;
+                const CV<T> a = L[k * RP + p], b = L[m * RP + p];
+                CV<T>* o = out + (row0 + 2 * p) * nxp + k;
+                o[0] = CV<T>{T(0.5) * (a.x + b.x), T(0.5) * (a.y - b.y)};
+                if (2 * p + 1 < nr) o[nxp] = CV<T>{T(0.5) * (a.y + b.y), T(0.5) * (b.x - a.x)};
+            } else {
+                if (p >= nr) break;
+                out[(row0 + p) * nxp + k] = L[k * RP + p];
+            }
         }
     }
 }
 
 // The half spectrum back to rows of reals (unscaled); the imaginary parts of
 // the mean and of the highest wave of an even row do not count.
-template <bool P2, typename T, int CW, int VPT, int NT>
+template <bool P2, bool PAIR, typename T, int CW, int VPT, int NT>
 __global__ void __launch_bounds__(NT, 4)
 k_fft_rows_back(FftLine f, const CV<T>* __restrict__ in, T* __restrict__ out, int nxp,
                 int64_t nrows)
 {
-    constexpr int RP = CW + 1;
+    constexpr int RP = CW + 1, ROWS = PAIR ? 2 * CW : CW;
     extern __shared__ __align__(16) unsigned char smem[];
     CV<T>* tw = reinterpret_cast<CV<T>*>(smem);
     CV<T>* L = tw + f.n;
     const int tid = threadIdx.x, n = f.n;
-    const int64_t row0 = (int64_t)blockIdx.x * (2 * CW);
-    const int nr = nrows - row0 < 2 * CW ? (int)(nrows - row0) : 2 * CW;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
+    const int nr = nrows - row0 < ROWS ? (int)(nrows - row0) : ROWS;
     Twiddles<T, NT> wt;
     wt.load(f, tid);
-    // conj of Z = A + i B at k and n - k
+    // conj of Z = A + i B (PAIR; else of A) at k and n - k
     for (int k = tid; k <= n / 2; k += NT) {
         const bool real = k == 0 || 2 * k == n;
-        CV<T> v[2 * CW];
+        CV<T> v[ROWS];
 #pragma unroll
-        for (int r = 0; r < 2 * CW; ++r) {
+        for (int r = 0; r < ROWS; ++r) {
             v[r] = CV<T>{T(0), T(0)};
             if (r < nr) v[r] = in[(row0 + r) * nxp + k];
             if (real) v[r].y = T(0);
         }
 #pragma unroll
         for (int p = 0; p < CW; ++p) {
-            const CV<T> a = v[2 * p], b = v[2 * p + 1];
-            L[k * RP + p] = CV<T>{a.x - b.y, -(a.y + b.x)};
-            if (!real) L[(n - k) * RP + p] = CV<T>{a.x + b.y, a.y - b.x};
+            if constexpr (PAIR) {
+                const CV<T> a = v[2 * p], b = v[2 * p + 1];
+                L[k * RP + p] = CV<T>{a.x - b.y, -(a.y + b.x)};
+                if (!real) L[(n - k) * RP + p] = CV<T>{a.x + b.y, a.y - b.x};
+            } else {
+                L[k * RP + p] = CV<T>{v[p].x, -v[p].y};
+                if (!real) L[(n - k) * RP + p] = v[p];
+            }
         }
     }
     wt.store(tw, f, tid);
@@ -395,8 +437,12 @@ k_fft_rows_back(FftLine f, const CV<T>* __restrict__ in, T* __restrict__ out, in
 #pragma unroll
         for (int p = 0; p < CW; ++p) {
             const CV<T> v = L[x * RP + p];
-            if (2 * p < nr) out[(row0 + 2 * p) * n + x] = v.x;
-            if (2 * p + 1 < nr) out[(row0 + 2 * p + 1) * n + x] = -v.y;
+            if constexpr (PAIR) {
+                if (2 * p < nr) out[(row0 + 2 * p) * n + x] = v.x;
+                if (2 * p + 1 < nr) out[(row0 + 2 * p + 1) * n + x] = -v.y;
+            } else if (p < nr) {
+                out[(row0 + p) * n + x] = v.x;
+            }
         }
     }
 }
@@ -489,19 +535,31 @@ hipError_t launch_fft_rows(hipStream_t st, const FftLine& f, const void* in, voi
     return fft_row_shape<T>(f.n, [&](auto cw, auto vpt, auto nt) {
         constexpr int CW = decltype(cw)::value, V = decltype(vpt)::value, NT = decltype(nt)::value;
         const size_t lds = (size_t)f.n * (CW + 2) * sizeof(CV<T>);
-        const unsigned nwg = (unsigned)((nrows + 2 * CW - 1) / (2 * CW));
-        hipError_t e;
-        if (inverse) {
-            const auto k = f.p2 ? k_fft_rows_back<true, T, CW, V, NT> : k_fft_rows_back<false, T, CW, V, NT>;
-            if ((e = fft_lds(k, lds)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(nwg), dim3(NT), lds, st, f, (const CV<T>*)in, (T*)out, nxp,
+        // Two rows in a line cost a rounding each way, which in single precision and
+        // on rows of odd length the library's transforms do not have (they halve
+        // even ones): those go one by one.  RMS error of a solve, before the own
+        // transforms, with rows in pairs, one by one: 81 x 75 x 60 1.95, 2.06, 1.95
+        // (1e-7 of the rms), 25 x 15 x 9 1.58, 1.66, 1.53; 243^3 takes 251 us for
+        // 215, 125^3 67 for 66 (894 and 128 in the library).
+        const bool pair = sizeof(T) == 8 || f.n % 2 == 0;
+        const int rows = pair ? 2 * CW : CW;
+        const unsigned nwg = (unsigned)((nrows + rows - 1) / rows);
+        auto back = f.p2 ? k_fft_rows_back<true, true, T, CW, V, NT>
+                         : k_fft_rows_back<false, true, T, CW, V, NT>;
+        auto forth = f.p2 ? k_fft_rows<true, true, T, CW, V, NT> : k_fft_rows<false, true, T, CW, V, NT>;
+        if constexpr (sizeof(T) == 4)
+            if (!pair) {
+                back = k_fft_rows_back<false, false, T, CW, V, NT>;
+                forth = k_fft_rows<false, false, T, CW, V, NT>;
+            }
+        const hipError_t e = inverse ? fft_lds(back, lds) : fft_lds(forth, lds);
+        if (e != hipSuccess) return e;
+        if (inverse)
+            hipLaunchKernelGGL(back, dim3(nwg), dim3(NT), lds, st, f, (const CV<T>*)in, (T*)out, nxp,
                                nrows);
-        } else {
-            const auto k = f.p2 ? k_fft_rows<true, T, CW, V, NT> : k_fft_rows<false, T, CW, V, NT>;
-            if ((e = fft_lds(k, lds)) != hipSuccess) return e;
-            hipLaunchKernelGGL(k, dim3(nwg), dim3(NT), lds, st, f, (const T*)in, (CV<T>*)out, nxp,
+        else
+            hipLaunchKernelGGL(forth, dim3(nwg), dim3(NT), lds, st, f, (const T*)in, (CV<T>*)out, nxp,
                                nrows);
-        }
         return hipGetLastError();
     });
 }
