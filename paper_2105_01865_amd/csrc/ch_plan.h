@@ -498,14 +498,15 @@ inline ch_status plan_dt(Plan& P, double dt)
         // one whose fullest CU has least to do, a task costing its planes and 2.5
         // more (152 x 235 x 89 FP64: 12 planes 322 us, 10 planes 313).  Groups of
         // one wave already march further by the 2048 (64^3 FP64 with one row per
-        // task 88 us, 94 at half the march).  A batch does so where its x pass is
-        // one launch and the 2048 give it at most 5 planes (two boxes of 160 x 80
-        // x 40 FP64 172 -> 159 us, four of 65 x 119 x 29 201 -> 185); beyond, it
-        // gains nothing (two of 176 x 97 x 65 231 -> 235), and launches of one row
-        // mode each are short of groups (75 x 184 x 44 and 176 x 37 x 101 238 ->
-        // 253).
+        // task 88 us, 94 at half the march), and from 11 planes on nothing is gained
+        // (302 x 266 x 92 FP64 takes 1.2 % longer at 12 than at 11).  A batch does so
+        // where its x pass is one launch and the 2048 give it at most 5 planes (two
+        // boxes of 160 x 80 x 40 FP64 172 -> 159 us, four of 65 x 119 x 29 201 ->
+        // 185); beyond, it gains nothing (two of 176 x 97 x 65 231 -> 235), and
+        // launches of one row mode each are short of groups (75 x 184 x 44 and 176 x
+        // 37 x 101 238 -> 253).
         const bool one_launch = std::count(bmode.begin(), bmode.end(), bmode[0]) == P.nbox;
-        if (row_ok && zc <= (P.nbox == 1 ? 12 : 5) && one_launch) {
+        if (row_ok && zc <= (P.nbox == 1 ? 10 : 5) && one_launch) {
             const int64_t target = 1024 * 256 / std::max(64, P.x_threads);
             const int zn = (int)std::max<int64_t>(1, std::min<int64_t>(12, (rows_total / R + target / 2) / target));
             double best = INFINITY;

@@ -29,3 +29,14 @@ def test_batches_march_further_only_where_it_was_measured(shapes, longer):
         base = max(1, sum(s[0] * s[1] * s[2] for s in shapes) // nx // R // 2048)
         got = reported(shapes, 1e-4, prec)["z_chunk"]
         assert got > base if longer else got == base
+
+
+@pytest.mark.parametrize("shape", [(92, 266, 302), (154, 148, 234), (81, 320, 247)])
+def test_long_marches_stay(shape):
+    """Eleven planes and more by the 2048: one plane more or a better fit of the
+    last work-groups was measured to gain nothing."""
+    nz, ny, nx = shape
+    base = ny * nz // max(1, 256 // nx) // 2048
+    assert base >= 11
+    for prec in (0, 1):
+        assert reported([shape], 1e-4, prec)["z_chunk"] == min(16, base)
