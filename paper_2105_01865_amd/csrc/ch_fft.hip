@@ -7,12 +7,13 @@
 //   rows     2 CW rows of reals as CW complex lines (one row in the real, the
 //            next in the imaginary parts), separated on the way out; in single
 //            precision rows of odd length one by one
-//   columns  CW neighbouring columns (64 or 128 bytes), in place
+//   columns  CW neighbouring columns, in place: 8 (64 bytes in single, 128 in
+//            double precision), or 4 on single-precision lines over 512 points
 //   z solve  the same along z, forward, divided by the Laplacian's eigenvalues,
 //            and back: the spectrum is read and written once for what would be
 //            three passes
 // Lengths are products of 2, 3 and 5 up to FFT_MAX (fft_radices); other meshes
-// and those that are not better off here use the FFT library.
+// and those that are not better off here use the FFT library (own_lines).
 //
 // A line of n points goes through passes of radix 8, 6, 5, 4, 3 and 2 (Stockham's
 // self-sorting order): butterfly j of a pass takes the points j + r n/R, times
@@ -22,10 +23,12 @@
 // writes them.  The inverse transform is the forward one of the conjugate,
 // conjugated.
 //
-// What bounds it: memory (each pass's bytes at a copy's rate), with two or more
-// groups per CU so that one group's loads run under another's passes.  512^3 FP32
-// (537 MB in, 539 MB out a pass; copy 222 us): rows 209 us, columns 237, the z
-// solve 447 (planes 1.1 MB apart; before, two transforms and a division); the
+// What bounds it: memory, where two or more groups share a CU so that one group's
+// loads run under another's passes: lines of up to 512 points (two groups, LDS and
+// four waves per SIMD); in double precision beyond 512 one group takes up to 147 KB
+// of LDS.  512^3 FP32 (537 MB in, 539 MB out a pass; copy 222 us): rows 209 us,
+// columns 237; the z solve 447, planes 1.1 MB apart, where two groups on two XCDs
+// share each line of 128 bytes (before, two transforms and a division); the
 // whole periodic solve 2619 -> 1305 us.
 // 240 x 180 x 160 FP64: rows 25 us, columns 28, z 42, against 23, 44 and 79
 // (three passes) before.  Lengths that are powers of two have kernels without the
@@ -449,7 +452,9 @@ k_fft_rows_back(FftLine f, const CV<T>* __restrict__ in, T* __restrict__ out, in
 
 // ---- launchers --------------------------------------------------------------
 // Column shapes (columns, threads) by a line's points.  Eight points per thread
-// (sixteen spill).  Tiles of 64 bytes in FP32, so that two groups share a CU
+// (sixteen spill; of these only the z solve of double-precision lines of over 512
+// points that are no power of two does, 36 bytes a lane: 64 x 64 x 1000 124 us
+// a solve against 186 in the library).  Tiles of 64 bytes in FP32, so that two groups share a CU
 // (512^3: the transforms and the solve along walls 1623 us with 128-byte tiles of
 // 1024 threads, 1468 with these).  No more threads than eight points each ask
 // for: short lines leave the rest idle (640 x 30 x 32 FP64: 52 -> 48 us).

@@ -258,8 +258,9 @@ k_check_velocity(const chd::BoxDesc* __restrict__ boxes, int nbox, const T* __re
 // plane k), k fastest; each work-group takes a contiguous run of items
 // (XCD-contiguous runs), so consecutive items are neighbouring target planes
 // of one band, whose z stencils share most of their coarse planes: those
-// rows come from L2 (at 512^3, 234 -> 201 us per FP32 component inside a
-// step against the plane-major order):
+// rows come from L2 (at 512^3 from 256^2 coarse rows, which the marching kernel
+// takes now, 234 -> 201 us per FP32 component inside a step against the
+// plane-major order):
 //   A. the band's coarse rows, each combined over the 4 source planes of k's
 //      z stencil, into LDS (coalesced along x; MA rows' loads in flight per
 //      thread, through buffer resources on the 4 planes);
@@ -477,7 +478,8 @@ k_interp(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
 // caches cold, against the general kernel (three barriers and scalar loads of
 // the y stencil per item, the z stencil's rows through LDS): 512^3 FP32 169-182
 // against 202 us, FP64 331-340 against 379-383, 256^3 FP32 34 against 76, FP64
-// 54 against 114.
+// 54 against 114.  With selected taps and 11 rows it takes 256 registers in double
+// precision, one wave per SIMD; march_taken has what it is measured to gain where.
 constexpr int MARCH_ROWS = MARCH_BAND;
 // first tap of target q in its group
 template <int P>

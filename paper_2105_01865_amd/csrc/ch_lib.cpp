@@ -445,11 +445,12 @@ bool upload_weights(void** dptr, const std::vector<double>& w, int precision)
     return upload(dptr, f.data(), sizeof(float) * f.size());
 }
 
-// LDS per work-group the band height is chosen for: three groups per CU in
-// single precision, two in double, which admits bands of 32 (16) rows at the
-// 512^3-from-256^2 ratio; measured faster than more groups with half the
-// band, since each item's fixed cost (three barriers, one load round) then
-// covers fewer rows.  And the most one group may take.
+// LDS per work-group the general kernel's band height is chosen for: three groups
+// per CU in single precision, two in double, which admits bands of 32 (16) rows on
+// 256-point coarse rows at a ratio of two; measured there, before the marching
+// kernel took that shape, faster than more groups with half the band, since each
+// item's fixed cost (three barriers, one load round) then covers fewer rows.  And
+// the most one group may take.
 constexpr size_t interp_lds_target(size_t esize) { return esize == 4 ? 54528 : 81920; }
 constexpr size_t INTERP_LDS_MAX = 163840;
 
