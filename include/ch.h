@@ -378,7 +378,8 @@ ch_status ch_get_config(const ch_state* s, int cfg[8]);
 
 /* Which x-pass program the plan of a state (batch) runs, for reports and
  * tests (the arithmetic is the same in all): *kind = 0 the general program,
- * 1 the row program (one cell per thread, the y stencil in registers), 2 the
+ * 1 the row program (one cell per thread, the y stencil in registers; the
+ * explicit scheme has one of its own), 2 the
  * row program with several rows in some task, 3 the segmented program (x
  * lines longer than a work-group), 4 the row program in two or three
  * launches (a batch whose boxes take different row modes: one row per task,

@@ -103,3 +103,17 @@ def test_only_launched_shapes_of_columns_are_built():
     cols = [ln for ln in out.splitlines() if "k_fft_cols<" in ln or "k_fft_zsolve<" in ln]
     assert any("float, 4, 8, 512" in ln for ln in cols)
     assert not any("double, 4," in ln for ln in cols)
+
+
+def test_the_gpu_test_s_shapes_reach_every_radix_and_launch_shape():
+    from tests.test_gpu_fft_lines import LONG_Z, SHAPES
+    for p32, radices in ((0, {2, 3, 4, 5, 8}), (1, {2, 3, 4, 5, 6, 8})):
+        got = route([(s, 0, p32) for s in SHAPES + LONG_Z])
+        own = [(s, g) for s, g in zip(SHAPES + LONG_Z, got) if g[0]]
+        assert len(own) < len(got)          # and both sides of the rule
+        for axis in range(3):
+            assert set().union(*(g[2][axis] for _, g in own)) >= radices - {6}
+            lens = [s[2 - axis] for s, _ in own]
+            for lo, hi in ((1, 128), (128, 256), (256, 512), (512, 1024)):
+                assert any(lo < n <= hi for n in lens), (axis, lo)
+        assert any(6 in r for _, g in own for r in g[2]) == bool(p32)
