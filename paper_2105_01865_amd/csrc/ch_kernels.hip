@@ -1107,12 +1107,13 @@ k_ccl_sum(int* __restrict__ lab, int* __restrict__ cnt, const int* __restrict__ 
     const int n = meta[0] < cap ? meta[0] : cap;
     for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < n; e += gridDim.x * blockDim.x) {
         const int r = list[e];
-        int root = lab[r];
+        int root = lab[r], up = lab[root];   // most chains end here
         // labels only decrease along the chain, and a label read while its
         // owner shortens it is an ancestor either way: it ends at the root
-        for (int up = ccl_load<DEV>(lab, root); up != root; up = ccl_load<DEV>(lab, root)) {
+        while (up != root) {
             root = up;
             __hip_atomic_store(lab + r, root, __ATOMIC_RELAXED, DEV);
+            up = ccl_load<DEV>(lab, root);
         }
         if (root != r) atomicAdd(cnt + root, cnt[r]);
     }
