@@ -184,7 +184,9 @@ inline bool interp_piped(size_t esize, int rmax, int64_t sx)
 //     256 registers leave one wave per SIMD and up to half of the lanes idle and
 //     the general kernel stores 4 targets at once (256 to 384 columns 477 -> 615
 //     us, 132 to 220 75 -> 96); where it cannot, this one gains (435 columns 1409
-//     -> 844);
+//     -> 844).  One of its groups fills a CU, so neither where the last round of
+//     256 leaves a third of the CUs idle (96 x 96 x 64 to 152 x 152 x 96, 240
+//     groups, 70 -> 59 us; to 152 x 152 x 128, 320 groups, 80 -> 99);
 //   - in single precision not with 11 rows on large meshes where the general one
 //     is piped and stores 4 targets at once (256 x 256 x 160 to 384 x 384 x 240
 //     238 -> 252 us, to 436 x 436 x 272 286 -> 308; from 256 x 256 x 96 to 384 x
@@ -196,7 +198,9 @@ inline bool march_taken(size_t esize, int rm, int xp, int yp, const MarchShape& 
     const bool known = (xp == chk::MARCH_FACE && yp == chk::MARCH_CENTRE) ||
                        (xp == chk::MARCH_CENTRE && yp != chk::MARCH_ANY);
     if (known) return true;
-    if (m.nband * m.nchunk < 192) return false;
+    const int64_t groups = (int64_t)m.nband * m.nchunk;
+    if (groups < 192) return false;
+    if (rm == 11 && esize == 8 && 3 * groups < 2 * ((groups + 255) / 256 * 256)) return false;
     if (rm == 8 || tn[0] % 4 != 0) return true;
     return esize == 4 ? !piped || tn[0] * tn[1] * tn[2] < (1 << 25) : sx <= 128;
 }

@@ -16,7 +16,7 @@ from tests.test_transfer_route import routes
     ((770, 24, 60), (130, 8, 20), (True, True)),       # ratio 3, four sub-bands
     ((402, 31, 150), (150, 20, 96), (True, True)),     # ratio 1.5, two
     ((262, 25, 387), (100, 8, 129), (True, True)),     # ratio 3, one
-    ((262, 25, 211), (100, 16, 132), (True, True)),    # 11 rows, odd target rows
+    ((402, 25, 211), (100, 16, 132), (True, True)),    # 11 rows, odd target rows
     ((262, 24, 208), (100, 15, 130), (True, False)),   # 11 rows, rows of 4 targets
     ((50, 15, 320), (40, 12, 256), (False, False)),    # FP32: piped
     ((12, 230, 230), (12, 230, 230), (False, False)),  # ratio 1, piped

@@ -45,6 +45,11 @@ def routes(cases):
     # eleven rows in double precision: up to 128 points, or odd target rows
     ((128, 128, 128), (192, 192, 192), 8, 25, 11, True),
     ((160, 256, 256), (240, 384, 384), 8, 15, 11, False),
+    # ... and where the last round of 256 groups is at least two thirds of the CUs
+    ((64, 96, 96), (96, 152, 152), 8, 24, 11, True),       # 240 groups
+    ((64, 96, 96), (128, 152, 152), 8, 24, 11, False),     # 320
+    ((64, 128, 128), (128, 192, 192), 8, 25, 11, True),    # 384
+    ((24, 128, 256), (44, 192, 385), 8, 15, 11, False),    # 264, odd target rows
     ((160, 256, 256), (272, 435, 435), 8, 15, 11, True),
     # eleven rows in single precision: large piped shapes stay
     ((96, 256, 256), (144, 384, 384), 4, 16, 11, True),
