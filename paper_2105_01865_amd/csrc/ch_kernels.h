@@ -77,14 +77,18 @@ struct InterpArgs {
     const int* iz;          // 4 taps per target plane, z
     const void* wz;
     const int* band;
-    // the marching kernel (rm > 0): coarse rows held per thread (8 or 11), first
-    // y tap of each target row, threads per sub-band of 8 target rows (a
-    // multiple of 64), sub-bands per group, bands of groups, chunks of kc target
-    // planes
-    int rm, xp, yp;
-    const int* iy0;
-    int sxw, nsub, nband, nchunk, kc;
-    int nt;                 // non-temporal stores
+};
+
+// What the marching kernel needs besides (apart from it: a longer argument block
+// costs the general kernel's start, 0.2 us a launch): coarse rows held per thread
+// (8 or 11; 0: the general kernel), the tap patterns, the first y tap of each
+// target row, threads per sub-band of 8 target rows (a multiple of 64), sub-bands
+// per group, bands of groups, chunks of kc target planes, non-temporal stores.
+struct MarchArgs {
+    int rm = 0, xp = 0, yp = 0;
+    const int* iy0 = nullptr;
+    int sxw = 0, nsub = 0, nband = 0, nchunk = 0, kc = 0;
+    int nt = 0;
 };
 
 // LDS of one transfer work-group: rmax coarse rows and jb target rows
@@ -94,7 +98,7 @@ constexpr size_t interp_lds(int rmax, int jb, int sx, size_t esize)
 }
 
 template <typename T>
-hipError_t launch_interp(hipStream_t st, const InterpArgs& a);
+hipError_t launch_interp(hipStream_t st, const InterpArgs& a, const MarchArgs& m);
 
 // Solenoidal transfer: the coarse normal gradient of component comp (0 u
 // along x, 1 v along y, 2 w along z) at the coarse cell centres, and the

@@ -490,7 +490,7 @@ constexpr int march_tap(int q)
 
 template <typename T, int RM, int XP, int YP>
 __global__ void __launch_bounds__(256)
-k_interp_march(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
+k_interp_march(InterpArgs a, MarchArgs m, const T* __restrict__ src, T* __restrict__ dst,
                const int* __restrict__ iy0, const int* __restrict__ izt,
                const T* __restrict__ wzt, const T* __restrict__ wyt,
                const int* __restrict__ ixt, const double* __restrict__ wxt)
@@ -502,22 +502,22 @@ k_interp_march(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
     extern __shared__ __align__(16) unsigned char smem[];
     T* yr = reinterpret_cast<T*>(smem);   // 2 x (nsub MR) x sx
     constexpr uint32_t sT = sizeof(T);
-    const int sx = a.sx, nsub = a.nsub, nt = 256;
+    const int sx = a.sx, nsub = m.nsub, nt = 256;
     const int tid = threadIdx.x;
     const uint32_t pbytes = (uint32_t)(a.plane * sizeof(T));
     const int wg = xcd_task(blockIdx.x, gridDim.x);
-    const int bandi = wg / a.nchunk, chunk = wg - bandi * a.nchunk;
-    const int k0 = chunk * a.kc, k1 = k0 + a.kc < a.tnz ? k0 + a.kc : a.tnz;
+    const int bandi = wg / m.nchunk, chunk = wg - bandi * m.nchunk;
+    const int k0 = chunk * m.kc, k1 = k0 + m.kc < a.tnz ? k0 + m.kc : a.tnz;
     const int j0 = bandi * MR * nsub;                          // the group's target rows
     const int njw = a.tny - j0 < MR * nsub ? a.tny - j0 : MR * nsub;
     const int bufsz = MR * nsub * sx;
 
     // y stencil of this wave's sub-band: coarse rows base, base + 1, ... (cyclic),
     // the taps of target row jj from row l[jj] of them on
-    const int sub = chd::uniform_i(tid / a.sxw);
+    const int sub = chd::uniform_i(tid / m.sxw);
     const int js = j0 + MR * sub;
     const bool wact = sub < nsub && js < a.tny;
-    const int cx = tid - sub * a.sxw;
+    const int cx = tid - sub * m.sxw;
     const bool cact = wact && cx < sx;
     const int jb = wact ? js : 0;
     const int base = iy0[jb];
@@ -640,7 +640,7 @@ k_interp_march(InterpArgs a, const T* __restrict__ src, T* __restrict__ dst,
                 }
                 T* o = out + (int64_t)jj * a.tnx;
                 if (vec) {
-                    if (a.nt)
+                    if (m.nt)
                         __builtin_nontemporal_store(T4{y[0], y[1], y[2], y[3]},
                                                     reinterpret_cast<T4*>(o));
                     else
@@ -1821,15 +1821,15 @@ static hipError_t launch_interp_jb(hipStream_t st, const InterpArgs& a)
 }
 
 template <typename T>
-hipError_t launch_interp(hipStream_t st, const InterpArgs& a)
+hipError_t launch_interp(hipStream_t st, const InterpArgs& a, const MarchArgs& m)
 {
-    if (a.rm) {
-        const dim3 grid((unsigned)(a.nband * a.nchunk));
-        const size_t lds = (size_t)2 * MARCH_ROWS * a.nsub * a.sx * sizeof(T);
+    if (m.rm) {
+        const dim3 grid((unsigned)(m.nband * m.nchunk));
+        const size_t lds = (size_t)2 * MARCH_ROWS * m.nsub * a.sx * sizeof(T);
         auto go = [&](auto rm, auto xp, auto yp) {
             hipLaunchKernelGGL((k_interp_march<T, decltype(rm)::value, decltype(xp)::value,
                                                decltype(yp)::value>),
-                               grid, dim3(256), lds, st, a, (const T*)a.src, (T*)a.dst, a.iy0, a.iz,
+                               grid, dim3(256), lds, st, a, m, (const T*)a.src, (T*)a.dst, m.iy0, a.iz,
                                (const T*)a.wz, (const T*)a.wy, a.ix, a.wx);
             return hipGetLastError();
         };
@@ -1837,11 +1837,11 @@ hipError_t launch_interp(hipStream_t st, const InterpArgs& a)
         constexpr IC<MARCH_ANY> any{};
         constexpr IC<MARCH_FACE> face{};
         constexpr IC<MARCH_CENTRE> centre{};
-        if (a.xp == MARCH_FACE && a.yp == MARCH_CENTRE) return go(IC<8>{}, face, centre);
-        if (a.xp == MARCH_CENTRE && a.yp == MARCH_FACE) return go(IC<7>{}, centre, face);
-        if (a.xp == MARCH_CENTRE && a.yp == MARCH_CENTRE) return go(IC<8>{}, centre, centre);
-        if (a.rm == 8) return go(IC<8>{}, any, any);
-        if (a.rm == 11) return go(IC<11>{}, any, any);
+        if (m.xp == MARCH_FACE && m.yp == MARCH_CENTRE) return go(IC<8>{}, face, centre);
+        if (m.xp == MARCH_CENTRE && m.yp == MARCH_FACE) return go(IC<7>{}, centre, face);
+        if (m.xp == MARCH_CENTRE && m.yp == MARCH_CENTRE) return go(IC<8>{}, centre, centre);
+        if (m.rm == 8) return go(IC<8>{}, any, any);
+        if (m.rm == 11) return go(IC<11>{}, any, any);
         return hipErrorInvalidValue;
     }
     switch (a.jb) {
@@ -2021,8 +2021,8 @@ template hipError_t launch_check_velocity<double>(hipStream_t, const chd::BoxDes
                                                   const void*, const void*, const void*, int*);
 template hipError_t launch_check_velocity<float>(hipStream_t, const chd::BoxDesc*, int,
                                                  const void*, const void*, const void*, int*);
-template hipError_t launch_interp<double>(hipStream_t, const InterpArgs&);
-template hipError_t launch_interp<float>(hipStream_t, const InterpArgs&);
+template hipError_t launch_interp<double>(hipStream_t, const InterpArgs&, const MarchArgs&);
+template hipError_t launch_interp<float>(hipStream_t, const InterpArgs&, const MarchArgs&);
 template hipError_t launch_drops<double>(hipStream_t, const void*, int, int, int, const int*,
                                          double, int*, int*, int*, int*, int, int*);
 template hipError_t launch_drops<float>(hipStream_t, const void*, int, int, int, const int*,

@@ -514,20 +514,21 @@ hipError_t launch_transfer(const Transfer& t, hipStream_t st, const void* src, v
     ia.iz = t.idx[2];
     ia.wz = t.wz;
     ia.band = t.band;
-    ia.rm = t.rm;
-    ia.xp = t.xp;
-    ia.yp = t.yp;
-    ia.iy0 = t.iy0;
+    chk::MarchArgs ma;
     if (t.rm) {
         const chp::MarchShape m = chp::march_shape(sizeof(T), t.sx, t.tn);
-        ia.sxw = m.sxw;
-        ia.nsub = m.nsub;
-        ia.nband = m.nband;
-        ia.kc = m.kc;
-        ia.nchunk = m.nchunk;
-        ia.nt = m.nt;
+        ma.rm = t.rm;
+        ma.xp = t.xp;
+        ma.yp = t.yp;
+        ma.iy0 = t.iy0;
+        ma.sxw = m.sxw;
+        ma.nsub = m.nsub;
+        ma.nband = m.nband;
+        ma.kc = m.kc;
+        ma.nchunk = m.nchunk;
+        ma.nt = m.nt;
     }
-    return chk::launch_interp<T>(st, ia);
+    return chk::launch_interp<T>(st, ia, ma);
 }
 
 // One component of the solenoidal transfer: its coarse normal gradient, that
